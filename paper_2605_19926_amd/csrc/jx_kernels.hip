@@ -7,8 +7,8 @@
 //      Table 1 and Table 2 of the paper);
 //   3. on done, reset the episode in place: spawn, heading, goal by BFS, door on
 //      a shortest path, key in the start region, decor.  BFS runs bit-parallel:
-//      lane y holds map row y as a 64-bit mask, one frontier expansion per
-//      iteration (shift within the row, lane shuffle across rows);
+//      lane y holds map row y as a bit mask, one frontier expansion per level
+//      (shift within the row, DPP move across rows);
 //   4. cast one ray per screen column (lane c takes columns c, c+64, ...) with
 //      DDA over tile boundaries (Sec. 2.1) through the LDS map, and reduce each
 //      column to a span record: wall colour, wall half-height in rows, nearest
@@ -100,26 +100,39 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint64_t shfl_idx64(uint64_t v, int src) {
-  uint32_t lo = __shfl((int)(uint32_t)v, src, 64);
-  uint32_t hi = __shfl((int)(uint32_t)(v >> 32), src, 64);
-  return ((uint64_t)hi << 32) | lo;
+// Cross-lane moves by DPP: a lane shuffle through LDS (ds_bpermute) costs an LDS
+// round trip, a DPP move one VALU instruction.  Lanes without a source read 0.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, ROWS == 0xF);
 }
-__device__ __forceinline__ uint64_t shfl_up64(uint64_t v, int d) {
-  uint32_t lo = __shfl_up((int)(uint32_t)v, d, 64);
-  uint32_t hi = __shfl_up((int)(uint32_t)(v >> 32), d, 64);
-  return ((uint64_t)hi << 32) | lo;
+constexpr int kDppRowShr = 0x110, kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138, kDppBcast15 = 0x142,
+              kDppBcast31 = 0x143;
+// lane i takes lane i - 1's (prev) or lane i + 1's (next) value
+__device__ __forceinline__ uint32_t lane_prev(uint32_t v) { return dpp<kDppWaveShr1>(v); }
+__device__ __forceinline__ uint32_t lane_next(uint32_t v) { return dpp<kDppWaveShl1>(v); }
+__device__ __forceinline__ uint64_t lane_prev(uint64_t v) {
+  return ((uint64_t)lane_prev((uint32_t)(v >> 32)) << 32) | lane_prev((uint32_t)v);
 }
-__device__ __forceinline__ uint64_t shfl_down64(uint64_t v, int d) {
-  uint32_t lo = __shfl_down((int)(uint32_t)v, d, 64);
-  uint32_t hi = __shfl_down((int)(uint32_t)(v >> 32), d, 64);
-  return ((uint64_t)hi << 32) | lo;
+__device__ __forceinline__ uint64_t lane_next(uint64_t v) {
+  return ((uint64_t)lane_next((uint32_t)(v >> 32)) << 32) | lane_next((uint32_t)v);
 }
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t o = (uint32_t)__shfl_up((int)v, d, 64);
-    if (lane >= d) v += o;
-  }
+// lane src's value (src uniform), in scalar registers
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int src) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, src & 63);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int src) {
+  return ((uint64_t)lane_value((uint32_t)(v >> 32), src) << 32) | lane_value((uint32_t)v, src);
+}
+// Inclusive prefix sum over the wave: within each row of 16 lanes, then row
+// totals to the odd rows, then the lower half's total to the upper half.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  v += dpp<kDppRowShr + 1>(v);
+  v += dpp<kDppRowShr + 2>(v);
+  v += dpp<kDppRowShr + 4>(v);
+  v += dpp<kDppRowShr + 8>(v);
+  v += dpp<kDppBcast15, 0xA>(v);
+  v += dpp<kDppBcast31, 0xC>(v);
   return v;
 }
 __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0ull; }
@@ -135,6 +148,8 @@ __device__ __forceinline__ double uniform_d(double v) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 // ---- SplitMix64 (Steele, Lea & Flood 2014) --------------------------------------
 __device__ __forceinline__ uint64_t sm_next(uint64_t& s) {
   s += 0x9E3779B97F4A7C15ull;
@@ -148,58 +163,119 @@ __device__ __forceinline__ uint32_t sm_draw(uint64_t& s, uint32_t n) {
   return (uint32_t)(((sm_next(s) >> 32) * (uint64_t)n) >> 32);
 }
 
-// ---- row-mask set operations (lane y < N holds row y) ---------------------------
+// ---- row-mask set operations (lane y < N holds row y; M has at least N bits) -----
+__device__ __forceinline__ uint32_t bits_of(uint32_t m) { return (uint32_t)__popc(m); }
+__device__ __forceinline__ uint32_t bits_of(uint64_t m) { return (uint32_t)__popcll(m); }
+__device__ __forceinline__ int first_bit(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int first_bit(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
+
 // Tile id of the r-th set bit in row-major order of the distributed mask.
-__device__ int mask_select(uint64_t m, uint32_t r, int N, int lane) {
-  uint32_t c = (uint32_t)__popcll(m);
-  uint32_t incl = wave_incl_scan(c, lane);
-  uint32_t excl = incl - c;
-  uint64_t own = __ballot(r >= excl && r < incl);
-  int L = __ffsll((unsigned long long)own) - 1;
-  uint64_t mm = shfl_idx64(m, L);
-  uint32_t k = r - (uint32_t)__shfl((int)excl, L, 64);
+template <typename M>
+__device__ int mask_select(M m, uint32_t r, int N) {
+  const uint32_t c = bits_of(m), incl = wave_incl_scan(c), excl = incl - c;
+  const int L = first_bit((uint64_t)__ballot(r >= excl && r < incl));
+  M mm = lane_value(m, L);
+  const uint32_t k = r - lane_value(excl, L);
   for (uint32_t i = 0; i < k; ++i) mm &= mm - 1;
-  return L * N + (__ffsll((unsigned long long)mm) - 1);
+  return L * N + first_bit(mm);
 }
-__device__ __forceinline__ uint32_t mask_count(uint64_t m, int lane) {
-  uint32_t incl = wave_incl_scan((uint32_t)__popcll(m), lane);
-  return (uint32_t)__shfl((int)incl, 63, 64);
+template <typename M>
+__device__ __forceinline__ uint32_t mask_count(M m) {
+  return lane_value(wave_incl_scan(bits_of(m)), 63);
 }
-__device__ __forceinline__ int mask_first(uint64_t m, int N) {
-  uint64_t own = __ballot(m != 0ull);
+template <typename M>
+__device__ __forceinline__ int mask_first(M m, int N) {
+  const uint64_t own = __ballot(m != 0);
   if (own == 0ull) return -1;
-  int L = __ffsll((unsigned long long)own) - 1;
-  uint64_t mm = shfl_idx64(m, L);
-  return L * N + (__ffsll((unsigned long long)mm) - 1);
+  const int L = first_bit(own);
+  return L * N + first_bit(lane_value(m, L));
 }
-__device__ __forceinline__ uint64_t bit_of(int id, int N, int lane) {
-  return (id >= 0 && lane == id / N) ? (1ull << (id % N)) : 0ull;
+template <typename M>
+__device__ __forceinline__ M bit_of(int id, int N, int lane) {
+  return (id >= 0 && lane == id / N) ? ((M)1 << (id % N)) : (M)0;
 }
 
+// One level of a level-synchronous search: the tiles of U (passable, not yet
+// reached) beside the frontier F; they leave U.
+template <typename M>
+__device__ __forceinline__ M bfs_level(M F, M& U) {
+  const M nf = ((F << 1) | (F >> 1) | lane_prev(F) | lane_next(F)) & U;
+  U &= ~nf;
+  return nf;
+}
+
+template <typename M>
 struct Bfs {
-  int level;
-  uint64_t frontier;
-  uint64_t visited;
+  int level;    // of the farthest tiles
+  M frontier;   // the farthest tiles
+  M unreached;  // passable tiles the search did not reach
 };
-// Level-synchronous BFS over the passable mask; stops after `stop` levels
-// (stop < 0: until the frontier empties).  Every wave reaches the exit: the
-// visited set grows each iteration and is bounded by the map.
-__device__ Bfs bfs_rows(uint64_t pass, int src, int N, int stop, int lane) {
-  uint64_t F = bit_of(src, N, lane);
-  uint64_t V = F;
-  int level = 0;
-  while (level != stop) {
-    uint64_t up = shfl_up64(F, 1);
-    uint64_t dn = shfl_down64(F, 1);
-    if (lane == 0) up = 0ull;
-    if (lane == 63) dn = 0ull;
-    uint64_t nf = ((F << 1) | (F >> 1) | up | dn) & pass & ~V;
-    if (!wave_any(nf != 0ull)) break;
-    V |= nf;
-    F = nf;
-    ++level;
+// Search over the passable mask until the frontier empties.  A reset's time is
+// this serial chain (a 32-side maze has 100 to 300 levels, a 64-side one up to
+// about 1000, and a key-door reset searches three times), and one wave's chain
+// makes a whole per-step launch end late.  So a level is 7 VALU instructions
+// with 32-bit rows and 15 with 64-bit rows, and the wave asks only every fourth
+// level whether the search has ended.  Against lane shuffles through LDS on
+// 64-bit rows and a test per level, a step of 8192 32-side key-door envs with 8
+// resets fell from 122 to 56 us (41 us without any reset), one of 4096 16-side
+// mazes from 19.9 to 15.5 us.  Every wave reaches the exit: U shrinks with every
+// level that is not empty.
+template <typename M>
+__device__ Bfs<M> bfs_all(M pass, int src, int N, int lane) {
+  M f0, f1, f2, f3, f4 = bit_of<M>(src, N, lane);
+  M U = pass & ~f4;
+  int level = -4;
+  do {
+    f0 = f4;
+    f1 = bfs_level(f0, U);
+    f2 = bfs_level(f1, U);
+    f3 = bfs_level(f2, U);
+    f4 = bfs_level(f3, U);
+    level += 4;
+  } while (wave_any(f4 != 0));
+  if (wave_any(f3 != 0)) return {level + 3, f3, U};
+  if (wave_any(f2 != 0)) return {level + 2, f2, U};
+  if (wave_any(f1 != 0)) return {level + 1, f1, U};
+  return {level, f0, U};
+}
+
+// Tiles at distance h from a and at distance h + odd from b (both searches have
+// that many levels); the two chains run side by side.
+template <typename M>
+__device__ M bfs_meet(M pass, int a, int b, int h, int odd, int N, int lane) {
+  M Fa = bit_of<M>(a, N, lane), Fb = bit_of<M>(b, N, lane);
+  M Ua = pass & ~Fa, Ub = pass & ~Fb;
+  for (int i = 0; i < h; ++i) {
+    Fa = bfs_level(Fa, Ua);
+    Fb = bfs_level(Fb, Ub);
   }
-  return {level, F, V};
+  if (odd) Fb = bfs_level(Fb, Ub);
+  return Fa & Fb;
+}
+
+// Row masks of the tiles that `test` marks (bit 7 of each byte of a dword of 4
+// tiles): each lane turns 8 tiles into one byte of a row-major bit string in
+// LDS, then lane y takes its N bits from it.  `lbits` holds 516 bytes.
+template <typename M, typename T>
+__device__ __forceinline__ M row_masks(const uint8_t* lmap, uint32_t* lbits, int N, int lane, T&& test) {
+  const int NN = N * N;
+  const u32x2* l2 = reinterpret_cast<const u32x2*>(lmap);
+  auto four = [](uint32_t b7) { return ((b7 >> 7) * 0x01020408u >> 24) & 15u; };  // byte k's bit 7 -> bit k
+  for (int k = lane; 8 * k < NN; k += 64) {
+    const u32x2 v = l2[k];
+    reinterpret_cast<uint8_t*>(lbits)[k] = (uint8_t)(four(test(v.x)) | (four(test(v.y)) << 4));
+  }
+  wave_sync();
+  M m = 0;
+  if (lane < N) {
+    const uint32_t at = (uint32_t)(lane * N), sh = at & 31u;
+    const uint32_t* w = lbits + (at >> 5);
+    uint64_t v = __builtin_amdgcn_alignbit(w[1], w[0], sh);
+    if (sizeof(M) == 8) v |= (uint64_t)__builtin_amdgcn_alignbit(w[2], w[1], sh) << 32;
+    m = (M)(v & (~0ull >> (64 - N)));
+  }
+  wave_sync();
+  return m;
 }
 
 struct Episode {
@@ -208,83 +284,78 @@ struct Episode {
 };
 
 // Episode reset for episode `e` of the env with layout in `lmap` (0 floor).
+// M: row masks (32 bits where the map is at most 32 wide).
 // ASC: the batch may hold ASCII maps (else that code is compiled out).
-template <bool ASC>
-__device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint64_t seed, uint32_t e,
+template <bool ASC, typename M>
+__device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint32_t* lbits, uint64_t seed, uint32_t e,
                                  int lane) {
   const int N = cf.side;
   uint64_t s = seed ^ sm_mix((uint64_t)e + 1ull);
-  // lane y: row y as bit masks of floor tiles, spawn and goal candidates, doors
-  uint64_t freem = 0ull, spawnm = 0ull, goalm = 0ull, doorm = 0ull;
-  if (lane < N) {
-    const uint8_t* row = lmap + lane * N;
-    for (int xx = 0; xx < N; ++xx) {
-      const uint32_t v = row[xx];
-      const uint64_t bit = 1ull << xx;
-      if ((v & 0x8Fu) == 0u) {
-        freem |= bit;
-        if (v & kTileSpawn) spawnm |= bit;
-        if (v & kTileGoal) goalm |= bit;
-      }
-      if (v & kTileDoor) doorm |= bit;
-    }
-  }
-  const uint32_t n_free = mask_count(freem, lane);
+  // floor tiles: no wall class and no door
+  auto is_free = [](uint32_t v) {
+    const uint32_t t = v & 0x8F8F8F8Fu;
+    return ~(((t & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | t) & 0x80808080u;
+  };
+  const M freem = row_masks<M>(lmap, lbits, N, lane, is_free);
+  const uint32_t n_free = mask_count(freem);
   Episode ep;
   if (ASC && cf.ascii) {
     // ASCII maps: spawn among the spawn candidates (every floor tile if none),
     // heading, goal among the goal candidates (else the farthest tile from the
     // spawn with doors passable, smallest id); keys and doors come from the map
-    const uint32_t n_s = mask_count(spawnm, lane);
-    const int spawn = n_s ? mask_select(spawnm, sm_draw(s, n_s), N, lane)
-                          : mask_select(freem, sm_draw(s, n_free), N, lane);
+    const M spawnm = row_masks<M>(lmap, lbits, N, lane, [&](uint32_t v) { return is_free(v) & (v << 2); });
+    const M goalm = row_masks<M>(lmap, lbits, N, lane, [&](uint32_t v) { return is_free(v) & (v << 1); });
+    const uint32_t n_s = mask_count(spawnm);
+    const int spawn = n_s ? mask_select(spawnm, sm_draw(s, n_s), N) : mask_select(freem, sm_draw(s, n_free), N);
     const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
     ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
     ep.x = (float)(spawn % N) + 0.5f;
     ep.y = (float)(spawn / N) + 0.5f;
-    const uint32_t n_g = mask_count(goalm, lane);
-    ep.goal = n_g ? mask_select(goalm, sm_draw(s, n_g), N, lane)
-                  : mask_first(bfs_rows(freem | doorm, spawn, N, -1, lane).frontier, N);
+    const uint32_t n_g = mask_count(goalm);
+    if (n_g) {
+      ep.goal = mask_select(goalm, sm_draw(s, n_g), N);
+    } else {
+      const M doorm = row_masks<M>(lmap, lbits, N, lane, [](uint32_t v) { return v & 0x80808080u; });
+      ep.goal = mask_first(bfs_all<M>(freem | doorm, spawn, N, lane).frontier, N);
+    }
     ep.door = ep.key = -1;
     ep.nd = 0;
     ep.dec0 = ep.dec1 = -1;
     return ep;
   }
-  const int spawn = mask_select(freem, sm_draw(s, n_free), N, lane);
+  const int spawn = mask_select(freem, sm_draw(s, n_free), N);
   const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
   ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
   ep.x = (float)(spawn % N) + 0.5f;
   ep.y = (float)(spawn / N) + 0.5f;
 
-  Bfs b = bfs_rows(freem, spawn, N, -1, lane);
+  const Bfs<M> b = bfs_all<M>(freem, spawn, N, lane);
   const int L = b.level;
   ep.goal = mask_first(b.frontier, N);
   ep.door = -1;
   ep.key = -1;
+  const M spawnb = bit_of<M>(spawn, N, lane);
   if (cf.key_door && L >= 2) {
     const int h = L / 2;
-    Bfs a = bfs_rows(freem, spawn, N, h, lane);
-    Bfs g = bfs_rows(freem, ep.goal, N, L - h, lane);
-    ep.door = mask_first(a.frontier & g.frontier, N);
-    const uint64_t pass2 = freem & ~bit_of(ep.door, N, lane);
-    Bfs r = bfs_rows(pass2, spawn, N, -1, lane);
-    const uint64_t region = r.visited & ~bit_of(spawn, N, lane);
-    const uint32_t c = mask_count(region, lane);
-    ep.key = (c == 0) ? spawn : mask_select(region, sm_draw(s, c), N, lane);
+    ep.door = mask_first(bfs_meet<M>(freem, spawn, ep.goal, h, L & 1, N, lane), N);
+    const M pass2 = freem & ~bit_of<M>(ep.door, N, lane);
+    const M region = pass2 & ~bfs_all<M>(pass2, spawn, N, lane).unreached & ~spawnb;
+    const uint32_t c = mask_count(region);
+    ep.key = (c == 0) ? spawn : mask_select(region, sm_draw(s, c), N);
   }
   ep.nd = 0;
   ep.dec0 = -1;
   ep.dec1 = -1;
   if (cf.max_decor > 0) {
-    uint64_t cand = freem & ~bit_of(spawn, N, lane) & ~bit_of(ep.goal, N, lane) &
-                    ~bit_of(ep.key, N, lane) & ~bit_of(ep.door, N, lane);
-    const uint32_t C = mask_count(cand, lane);
+    M cand = freem & ~spawnb & ~bit_of<M>(ep.goal, N, lane) & ~bit_of<M>(ep.key, N, lane) &
+             ~bit_of<M>(ep.door, N, lane);
+    const uint32_t C = mask_count(cand);
     const int md = cf.max_decor > kMaxDecor ? kMaxDecor : cf.max_decor;
     int nd = (int)sm_draw(s, (uint32_t)(md + 1));
     if (nd > (int)C) nd = (int)C;
     for (int j = 0; j < nd; ++j) {
-      const int id = mask_select(cand, sm_draw(s, C - (uint32_t)j), N, lane);
-      cand &= ~bit_of(id, N, lane);
+      const int id = mask_select(cand, sm_draw(s, C - (uint32_t)j), N);
+      cand &= ~bit_of<M>(id, N, lane);
       if (j == 0) ep.dec0 = id;
       else ep.dec1 = id;
     }
@@ -294,7 +365,6 @@ __device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint64_t
 }
 
 typedef __attribute__((address_space(1))) uint32_t GlobalU32;
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x2 GlobalU32x2;
 typedef __attribute__((address_space(1))) u32x4 GlobalU32x4;
@@ -1048,7 +1118,9 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevI
   }
   if (mode == MODE_RESET || done) {
     const uint32_t e = (mode == MODE_RESET) ? 0u : ep + 1u;
-    const Episode n = episode_reset<ASC>(cf, lmap, seed, e, lane);
+    // (the span records of the previous frame are spent: their LDS is scratch here)
+    const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, uint32_t>(cf, lmap, lcol, seed, e, lane)
+                                            : episode_reset<ASC, uint64_t>(cf, lmap, lcol, seed, e, lane);
     x = n.x;
     y = n.y;
     th = n.th;
