@@ -139,14 +139,6 @@ __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0ull; }
 __device__ __forceinline__ uint32_t uniform_u(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-__device__ __forceinline__ float uniform_f(float v) {
-  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
-}
-__device__ __forceinline__ double uniform_d(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = uniform_u((uint32_t)b), hi = uniform_u((uint32_t)(b >> 32));
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -162,6 +154,18 @@ __device__ __forceinline__ uint64_t sm_mix(uint64_t v) { return sm_next(v); }
 __device__ __forceinline__ uint32_t sm_draw(uint64_t& s, uint32_t n) {
   return (uint32_t)(((sm_next(s) >> 32) * (uint64_t)n) >> 32);
 }
+
+// Row and column of a tile id (below 4096) on an N-wide map (N from 5 to 64) by
+// one multiplication: m = floor(2^18 / N) + 1 exceeds 2^18 / N by at most 1, so
+// id * m / 2^18 exceeds id / N by at most id / 2^18 < 1 / N (4095 * 64 < 2^18),
+// which never reaches the next integer.
+struct TileDiv {
+  int N;
+  uint32_t m;
+  __device__ __forceinline__ explicit TileDiv(int n) : N(n), m((1u << 18) / (uint32_t)n + 1u) {}
+  __device__ __forceinline__ int row(int id) const { return (int)(((uint32_t)id * m) >> 18); }
+  __device__ __forceinline__ int col(int id) const { return id - row(id) * N; }
+};
 
 // ---- row-mask set operations (lane y < N holds row y; M has at least N bits) -----
 __device__ __forceinline__ uint32_t bits_of(uint32_t m) { return (uint32_t)__popc(m); }
@@ -191,8 +195,8 @@ __device__ __forceinline__ int mask_first(M m, int N) {
   return L * N + first_bit(lane_value(m, L));
 }
 template <typename M>
-__device__ __forceinline__ M bit_of(int id, int N, int lane) {
-  return (id >= 0 && lane == id / N) ? ((M)1 << (id % N)) : (M)0;
+__device__ __forceinline__ M bit_of(int id, const TileDiv& td, int lane) {
+  return (id >= 0 && lane == td.row(id)) ? ((M)1 << td.col(id)) : (M)0;
 }
 
 // One level of a level-synchronous search: the tiles of U (passable, not yet
@@ -221,8 +225,8 @@ struct Bfs {
 // mazes from 19.9 to 15.5 us.  Every wave reaches the exit: U shrinks with every
 // level that is not empty.
 template <typename M>
-__device__ Bfs<M> bfs_all(M pass, int src, int N, int lane) {
-  M f0, f1, f2, f3, f4 = bit_of<M>(src, N, lane);
+__device__ Bfs<M> bfs_all(M pass, int src, const TileDiv& td, int lane) {
+  M f0, f1, f2, f3, f4 = bit_of<M>(src, td, lane);
   M U = pass & ~f4;
   int level = -4;
   do {
@@ -242,8 +246,8 @@ __device__ Bfs<M> bfs_all(M pass, int src, int N, int lane) {
 // Tiles at distance h from a and at distance h + odd from b (both searches have
 // that many levels); the two chains run side by side.
 template <typename M>
-__device__ M bfs_meet(M pass, int a, int b, int h, int odd, int N, int lane) {
-  M Fa = bit_of<M>(a, N, lane), Fb = bit_of<M>(b, N, lane);
+__device__ M bfs_meet(M pass, int a, int b, int h, int odd, const TileDiv& td, int lane) {
+  M Fa = bit_of<M>(a, td, lane), Fb = bit_of<M>(b, td, lane);
   M Ua = pass & ~Fa, Ub = pass & ~Fb;
   for (int i = 0; i < h; ++i) {
     Fa = bfs_level(Fa, Ua);
@@ -255,7 +259,7 @@ __device__ M bfs_meet(M pass, int a, int b, int h, int odd, int N, int lane) {
 
 // Row masks of the tiles that `test` marks (bit 7 of each byte of a dword of 4
 // tiles): each lane turns 8 tiles into one byte of a row-major bit string in
-// LDS, then lane y takes its N bits from it.  `lbits` holds 516 bytes.
+// LDS, then lane y takes its N bits from it.  `lbits` holds 512 bytes.
 template <typename M, typename T>
 __device__ __forceinline__ M row_masks(const uint8_t* lmap, uint32_t* lbits, int N, int lane, T&& test) {
   const int NN = N * N;
@@ -270,8 +274,10 @@ __device__ __forceinline__ M row_masks(const uint8_t* lmap, uint32_t* lbits, int
   if (lane < N) {
     const uint32_t at = (uint32_t)(lane * N), sh = at & 31u;
     const uint32_t* w = lbits + (at >> 5);
-    uint64_t v = __builtin_amdgcn_alignbit(w[1], w[0], sh);
-    if (sizeof(M) == 8) v |= (uint64_t)__builtin_amdgcn_alignbit(w[2], w[1], sh) << 32;
+    // (a row that fills its last word takes no bit from the one after it)
+    const bool more = sh + (uint32_t)N > (sizeof(M) == 8 ? 64u : 32u);
+    uint64_t v = __builtin_amdgcn_alignbit(sizeof(M) == 8 || more ? w[1] : 0u, w[0], sh);
+    if (sizeof(M) == 8) v |= (uint64_t)__builtin_amdgcn_alignbit(more ? w[2] : 0u, w[1], sh) << 32;
     m = (M)(v & (~0ull >> (64 - N)));
   }
   wave_sync();
@@ -287,8 +293,8 @@ struct Episode {
 // M: row masks (32 bits where the map is at most 32 wide).
 // ASC: the batch may hold ASCII maps (else that code is compiled out).
 template <bool ASC, typename M>
-__device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint32_t* lbits, uint64_t seed, uint32_t e,
-                                 int lane) {
+__device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint8_t* lmap, uint32_t* lbits, uint64_t seed,
+                                 uint32_t e, int lane) {
   const int N = cf.side;
   uint64_t s = seed ^ sm_mix((uint64_t)e + 1ull);
   // floor tiles: no wall class and no door
@@ -309,14 +315,14 @@ __device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint32_t
     const int spawn = n_s ? mask_select(spawnm, sm_draw(s, n_s), N) : mask_select(freem, sm_draw(s, n_free), N);
     const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
     ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
-    ep.x = (float)(spawn % N) + 0.5f;
-    ep.y = (float)(spawn / N) + 0.5f;
+    ep.x = (float)td.col(spawn) + 0.5f;
+    ep.y = (float)td.row(spawn) + 0.5f;
     const uint32_t n_g = mask_count(goalm);
     if (n_g) {
       ep.goal = mask_select(goalm, sm_draw(s, n_g), N);
     } else {
       const M doorm = row_masks<M>(lmap, lbits, N, lane, [](uint32_t v) { return v & 0x80808080u; });
-      ep.goal = mask_first(bfs_all<M>(freem | doorm, spawn, N, lane).frontier, N);
+      ep.goal = mask_first(bfs_all<M>(freem | doorm, spawn, td, lane).frontier, N);
     }
     ep.door = ep.key = -1;
     ep.nd = 0;
@@ -326,20 +332,20 @@ __device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint32_t
   const int spawn = mask_select(freem, sm_draw(s, n_free), N);
   const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
   ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
-  ep.x = (float)(spawn % N) + 0.5f;
-  ep.y = (float)(spawn / N) + 0.5f;
+  ep.x = (float)td.col(spawn) + 0.5f;
+  ep.y = (float)td.row(spawn) + 0.5f;
 
-  const Bfs<M> b = bfs_all<M>(freem, spawn, N, lane);
+  const Bfs<M> b = bfs_all<M>(freem, spawn, td, lane);
   const int L = b.level;
   ep.goal = mask_first(b.frontier, N);
   ep.door = -1;
   ep.key = -1;
-  const M spawnb = bit_of<M>(spawn, N, lane);
+  const M spawnb = bit_of<M>(spawn, td, lane);
   if (cf.key_door && L >= 2) {
     const int h = L / 2;
-    ep.door = mask_first(bfs_meet<M>(freem, spawn, ep.goal, h, L & 1, N, lane), N);
-    const M pass2 = freem & ~bit_of<M>(ep.door, N, lane);
-    const M region = pass2 & ~bfs_all<M>(pass2, spawn, N, lane).unreached & ~spawnb;
+    ep.door = mask_first(bfs_meet<M>(freem, spawn, ep.goal, h, L & 1, td, lane), N);
+    const M pass2 = freem & ~bit_of<M>(ep.door, td, lane);
+    const M region = pass2 & ~bfs_all<M>(pass2, spawn, td, lane).unreached & ~spawnb;
     const uint32_t c = mask_count(region);
     ep.key = (c == 0) ? spawn : mask_select(region, sm_draw(s, c), N);
   }
@@ -347,15 +353,15 @@ __device__ Episode episode_reset(const DevCfg& cf, const uint8_t* lmap, uint32_t
   ep.dec0 = -1;
   ep.dec1 = -1;
   if (cf.max_decor > 0) {
-    M cand = freem & ~spawnb & ~bit_of<M>(ep.goal, N, lane) & ~bit_of<M>(ep.key, N, lane) &
-             ~bit_of<M>(ep.door, N, lane);
+    M cand = freem & ~spawnb & ~bit_of<M>(ep.goal, td, lane) & ~bit_of<M>(ep.key, td, lane) &
+             ~bit_of<M>(ep.door, td, lane);
     const uint32_t C = mask_count(cand);
     const int md = cf.max_decor > kMaxDecor ? kMaxDecor : cf.max_decor;
     int nd = (int)sm_draw(s, (uint32_t)(md + 1));
     if (nd > (int)C) nd = (int)C;
     for (int j = 0; j < nd; ++j) {
       const int id = mask_select(cand, sm_draw(s, C - (uint32_t)j), N);
-      cand &= ~bit_of<M>(id, N, lane);
+      cand &= ~bit_of<M>(id, td, lane);
       if (j == 0) ep.dec0 = id;
       else ep.dec1 = id;
     }
@@ -441,6 +447,12 @@ __device__ __forceinline__ ColGroup col_group(const uint32_t* lcol, int cq) {
 
 // Crossings per batch of the DDA walk (one LDS round trip each).
 constexpr int kDdaBatch = 4;
+// A wave's map in LDS lies between two guards of blocking bytes, each as long as
+// the farthest a batch can step past a map of side MAXN: walks read without a
+// bounds check, and one that leaves the map stops on a guard.
+constexpr int guard_bytes(int maxn) { return kDdaBatch * maxn; }
+constexpr int map_slice(int maxn) { return maxn * maxn + 2 * guard_bytes(maxn); }
+typedef const __attribute__((address_space(3))) uint8_t* LdsBytes;
 
 constexpr uint32_t kCeil3[3] = {kCeil | (kCeil << 24), (kCeil >> 8) | (kCeil << 16),
                                 (kCeil >> 16) | (kCeil << 8)};
@@ -625,12 +637,21 @@ struct ColDbg {
 // Casts the env's columns and reduces each to a span record in lcol (and
 // writes debug records when asked).
 // dsn, dcs: sine and cosine of the heading in double.
+// col0, hop: this lane casts columns col0, col0 + hop, ...
+// The pose, the tiles and the flags are uniform across the wave.
+// A wave's time here is latency as much as issue (1,300 of a step's 5,500 cycles
+// in the walk of a 25-side map, 600 in the sprites, 800 in the rest): so guards
+// stand in for bounds checks, tile coordinates and palette indices come from one
+// multiplication each, and slots that hold nothing in front of the camera are
+// passed over.  With the same for the step, a fused step of 64 such envs fell
+// from 3.45 to 3.13 us, one of 8192 32 x 32 frames from 12.3 to 10.4 us.
 template <bool ASC>
-__device__ void render_columns(const DevCfg& cf, const DevIo& io, int env, int lane, uint8_t* lmap,
-                               const uint32_t* lclr,
-                               uint32_t* lcol, float x, float y, double dsn, double dcs, int goal,
-                               int door, int key, uint32_t fl, int nd, int dec0, int dec1,
+__device__ void render_columns(const DevCfg& cf, const TileDiv& td, const DevIo& io, int env, int col0, int hop,
+                               const uint8_t* lmap, const uint32_t* lclr, uint32_t* lcol, float x, float y, double dsn,
+                               double dcs, int goal, int door, int key, uint32_t fl, int nd, int dec0, int dec1,
                                uint32_t doors, int ak0, int ak1, int ak2) {
+  // every rounding is spelled out: products meet sums in fmaf where one rounding is meant
+#pragma clang fp contract(off)
   const int N = cf.side, H = cf.obs_h, W = cf.obs_w, K = cf.n_colors, S_lv = cf.shade_levels;
   // the shut locked door blocks rays like a wall (tile id `shut`, -1 if none)
   const int shut = (door >= 0 && !(fl & FL_DOOR_OPEN)) ? door : -1;
@@ -650,23 +671,22 @@ __device__ void render_columns(const DevCfg& cf, const DevIo& io, int env, int l
   const uint32_t srgb[4] = {asc ? kAKeyRgb[0] : kKeyRgb, asc ? kAKeyRgb[1] : kGoalRgb,
                             asc ? kAKeyRgb[2] : kDecorRgb, asc ? kGoalRgb : kDecorRgb};
   float sY[4], sU[4], sHW[4], sHS[4];
-  bool sVis[4];
+  uint32_t seen = 0u;  // bit j: slot j is in front of the camera
   const float halfW = 0.5f * (float)W;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    sVis[j] = false;
     sY[j] = sU[j] = sHW[j] = sHS[j] = 0.f;
     if (sid[j] < 0) continue;  // uniform across the wave
-    const int id = sid[j];
-    const float dx = ((float)(id % N) + 0.5f) - x;
-    const float dy = ((float)(id / N) + 0.5f) - y;
-    const float tY = dx * cs + dy * sn;
-    const float tX = dy * cs - dx * sn;
+    const float dx = ((float)td.col(sid[j]) + 0.5f) - x;
+    const float dy = ((float)td.row(sid[j]) + 0.5f) - y;
+    const float tY = fmaf(dx, cs, dy * sn);
+    if (!wave_any(tY > 0.05f)) continue;     // (every lane holds the same)
+    const float tX = fmaf(dy, cs, -(dx * sn));
     const float inv = 1.0f / tY;             // one division per sprite
     const float q = inv * cf.inv_tanH;       // 1 / (tanH tY)
+    seen |= 1u << j;
     sY[j] = tY;
-    sVis[j] = tY > 0.05f;
-    sU[j] = halfW * (1.0f + tX * q);
+    sU[j] = halfW * fmaf(tX, q, 1.0f);
     sHW[j] = halfW * 0.25f * q;
     sHS[j] = (float)H * 0.25f * inv;
   }
@@ -674,7 +694,13 @@ __device__ void render_columns(const DevCfg& cf, const DevIo& io, int env, int l
   const int ix0 = (int)floorf(x), iy0 = (int)floorf(y);
   const float halfH = (float)(H >> 1);
   const float INF = __builtin_huge_valf();
-  for (int col = lane; col < W; col += 64) {
+  const LdsBytes map0 = (LdsBytes)lmap;
+  const LdsBytes shutq = map0 + shut;
+  const uint32_t last = (uint32_t)(N * N - 1);
+  // hit / K by one multiplication (hit below 4096, K at most 8: hit times the
+  // excess of km over 2^16 / K stays below 2^16)
+  const uint32_t km = 65535u / (uint32_t)K + 1u;
+  for (int col = col0; col < W; col += hop) {
     // The ray components are formed in double and rounded once: dir and the
     // column's offset along `right` can nearly cancel, and a float sum would
     // then lose most of the component's digits.  Each float component is
@@ -682,10 +708,9 @@ __device__ void render_columns(const DevCfg& cf, const DevIo& io, int env, int l
     const double k = (double)(2 * col + 1 - W) * rq;
     const float rx = (float)fma(k, -dsn, dcs);
     const float ry = (float)fma(k, dcs, dsn);
-    const int ix = ix0, iy = iy0;
-    const int stx = rx > 0.f ? 1 : -1, sty = ry > 0.f ? 1 : -1;
-    const float Xn = (float)(rx > 0.f ? ix + 1 : ix);
-    const float Yn = (float)(ry > 0.f ? iy + 1 : iy);
+    const int stx = rx > 0.f ? 1 : -1, sty = ry > 0.f ? N : -N;
+    const float Xn = (float)(rx > 0.f ? ix0 + 1 : ix0);
+    const float Yn = (float)(ry > 0.f ? iy0 + 1 : iy0);
     const float ivx = __builtin_amdgcn_rcpf(rx), ivy = __builtin_amdgcn_rcpf(ry);
     // Ray parameter of the k-th x / y grid line ahead: t0 + k |1/r|, one fused
     // multiply-add from the crossing count (Xn - x is exact, 1/r within an
@@ -697,124 +722,117 @@ __device__ void render_columns(const DevCfg& cf, const DevIo& io, int env, int l
     float kx = 0.f, ky = 0.f;
     float tx = t0x, ty = t0y;
     float tst = INF;
-    int side = 0, hit = -1, cell = 1;
-    uint32_t hv = 1u;  // tile byte of the hit
+    bool xface = true;
     // Branch-free walk in batches: the sequence of tiles a ray crosses does
     // not depend on the map, only where it stops does.  Each batch computes
-    // the next kDdaBatch crossings (one grid line each: the tile index moves
-    // by +-1 on an x crossing, +-N on a y crossing, and that axis's crossing
-    // count by one), issues their LDS reads together and keeps the first
-    // blocking one, so a lane waits for one LDS round trip per batch instead
-    // of one per crossing.  The border of
-    // blocking tiles (checked on the host) stops every walk inside the map;
-    // crossings past the stop are discarded and read a clamped address.
-    const int dy = sty * N, NN = N * N;
-    int id = iy * N + ix;
-    const uint32_t last = (uint32_t)(NN - 1);
+    // the next kDdaBatch crossings (one grid line each: the tile moves by +-1
+    // on an x crossing, +-N on a y crossing, and that axis's crossing count by
+    // one), issues their LDS reads together and keeps the first blocking one,
+    // so a lane waits for one LDS round trip per batch instead of one per
+    // crossing.  The border of blocking tiles (checked on the host) stops every
+    // walk inside the map, and the guards one that starts in the border;
+    // crossings past the stop are discarded.
+    LdsBytes q = map0 + (iy0 * N + ix0), hitq = map0 - 1;
     bool found = false;
     for (int it = 0; it < 4 * N + 8 && !found; it += kDdaBatch) {
-      int ids[kDdaBatch];
+      LdsBytes qs[kDdaBatch];
       float ts[kDdaBatch];
-      bool sd[kDdaBatch];
+      bool sd[kDdaBatch], stop[kDdaBatch];
 #pragma unroll
       for (int u = 0; u < kDdaBatch; ++u) {
         const bool sx = tx < ty;
         ts[u] = sx ? tx : ty;
-        sd[u] = !sx;
-        id += sx ? stx : dy;
+        sd[u] = sx;
+        q += sx ? stx : sty;
         kx = sx ? kx + 1.f : kx;
         ky = sx ? ky : ky + 1.f;
         tx = fmaf(kx, dtx, t0x);
         ty = fmaf(ky, dty, t0y);
-        ids[u] = id;
+        qs[u] = q;
       }
-      // bit u: crossing u stops the walk (blocking tile, shut door, or off the map)
-      uint32_t stop = 0;
       uint32_t vs[kDdaBatch];
 #pragma unroll
-      for (int u = 0; u < kDdaBatch; ++u) {
-        const uint32_t uid = (uint32_t)ids[u];
-        vs[u] = lmap[uid < last ? uid : last];
-      }
+      for (int u = 0; u < kDdaBatch; ++u) vs[u] = *qs[u];
       if (asc) {
         // map doors block while their bit in `doors` is clear
 #pragma unroll
         for (int u = 0; u < kDdaBatch; ++u) {
           const uint32_t v = vs[u];
           const bool open = (v & kTileDoor) && ((doors >> (v & 15u)) & 1u);
-          stop |= (uint32_t)((((v & 0x8Fu) != 0u) && !open) | ((uint32_t)ids[u] > last)) << u;
+          stop[u] = ((v & 0x8Fu) != 0u) && !open;
         }
       } else {
 #pragma unroll
-        for (int u = 0; u < kDdaBatch; ++u)
-          stop |= (uint32_t)((vs[u] != 0u) | (ids[u] == shut) | ((uint32_t)ids[u] > last)) << u;
-      }
-      tst = ts[kDdaBatch - 1];  // kept only if nothing in the batch stops the walk
-      side = sd[kDdaBatch - 1] ? 1 : 0;
-      if (stop) {
-        int sid_ = ids[kDdaBatch - 1];
-        uint32_t sv = vs[kDdaBatch - 1];
+        for (int u = 0; u < kDdaBatch; ++u) stop[u] = vs[u] != 0u;
+        if (shut >= 0) {  // uniform
 #pragma unroll
-        for (int u = kDdaBatch - 2; u >= 0; --u) {  // the earliest stop wins
-          const bool b = (stop >> u) & 1u;
-          tst = b ? ts[u] : tst;
-          side = b ? (sd[u] ? 1 : 0) : side;
-          sid_ = b ? ids[u] : sid_;
-          sv = b ? vs[u] : sv;
+          for (int u = 0; u < kDdaBatch; ++u) stop[u] |= qs[u] == shutq;
         }
-        found = true;
-        const bool out = (uint32_t)sid_ > last;
-        hit = out ? -1 : sid_;
-        hv = out ? 1u : sv;
-        cell = (!out && (sid_ == shut || (hv & kTileDoor))) ? 2 : 1;
+      }
+#pragma unroll
+      for (int u = kDdaBatch - 1; u >= 0; --u) {  // the earliest stop wins
+        tst = stop[u] ? ts[u] : tst;
+        xface = stop[u] ? sd[u] : xface;
+        hitq = stop[u] ? qs[u] : hitq;
+        found |= stop[u];
       }
     }
-    uint32_t wc;
-    const uint32_t wcls = hv & 15u;
-    if (asc && (hv & kTileDoor)) wc = lclr[kClrDoor + ((hv >> 4) & 7u)];
-    else if (cell == 2) wc = kDoor;
-    else if (asc && wcls >= 2u && wcls <= 10u) wc = lclr[kClrWall9 + wcls - 2u];
-    else wc = lclr[kClrPalette + (hit < 0 ? 0 : hit) % K];
-    if (side) wc = (wc >> 1) & 0x7F7F7Fu;
+    const uint32_t hv = *hitq;  // the hit's tile byte (1 on a guard)
+    const uint32_t hid = (uint32_t)(hitq - map0);
+    const int hit = hid > last ? -1 : (int)hid;
+    const int cell = (hit >= 0 && (hit == shut || (hv & kTileDoor))) ? 2 : 1;
+    const uint32_t h = hit < 0 ? 0u : (uint32_t)hit;
+    uint32_t wc = lclr[kClrPalette + h - __umul24(__umul24(h, km) >> 16, (uint32_t)K)];
+    if (asc) {
+      const uint32_t wcls = hv & 15u;
+      if (hv & kTileDoor) wc = lclr[kClrDoor + ((hv >> 4) & 7u)];
+      else if (wcls >= 2u && wcls <= 10u) wc = lclr[kClrWall9 + wcls - 2u];
+    } else if (cell == 2) {
+      wc = kDoor;
+    }
+    if (!xface) wc = (wc >> 1) & 0x7F7F7Fu;
     if (S_lv > 0) {
       // distance shading: level l = min(floor(t* S / D), S - 1), each channel
       // scaled by (S - l) / S and rounded down; the division by S (numerators
       // below 4096) is a multiply by ceil(2^16 / S) and a shift
       const int lv = min((int)floorf(tst * cf.shade_scale), S_lv - 1);
       const uint32_t f = (uint32_t)(S_lv - lv), m = cf.shade_mul;
-      const uint32_t r = ((wc & 0xFFu) * f * m) >> 16;
-      const uint32_t g = (((wc >> 8) & 0xFFu) * f * m) >> 16;
-      const uint32_t b = (((wc >> 16) & 0xFFu) * f * m) >> 16;
+      const uint32_t r = __umul24(__umul24(wc & 0xFFu, f), m) >> 16;
+      const uint32_t g = __umul24(__umul24((wc >> 8) & 0xFFu, f), m) >> 16;
+      const uint32_t b = __umul24(__umul24((wc >> 16) & 0xFFu, f), m) >> 16;
       wc = r | (g << 8) | (b << 16);
     }
-    const float hh = halfH * __builtin_amdgcn_rcpf(tst);
-    const uint32_t wcount = (uint32_t)fminf(fmaxf(ceilf(hh - 0.5f), 0.f), halfH);
+    // rows at i + 0.5 < H / (2 t*): ceil(H / (2 t*) - 0.5) of them, at most H / 2
+    const float wrows = ceilf(fmaf(halfH, __builtin_amdgcn_rcpf(tst), -0.5f));
+    const uint32_t wcount = (uint32_t)__builtin_amdgcn_fmed3f(wrows, 0.f, halfH);
     // nearest covering sprite; on equal depth the later slot wins (painted last)
     float bestY = INF, bestHS = 0.f;
     uint32_t bestRgb = 0u;
     bool any = false;
-    const float cc = (float)col + 0.5f;
+    if (seen) {  // uniform
+      const float cc = (float)col + 0.5f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (sVis[j] && fabsf(cc - sU[j]) < sHW[j] && sY[j] < tst && sY[j] <= bestY) {
-        bestY = sY[j];
-        bestHS = sHS[j];
-        bestRgb = srgb[j];
-        any = true;
+      for (int j = 0; j < 4; ++j) {
+        if (!((seen >> j) & 1u)) continue;
+        if (fabsf(cc - sU[j]) < sHW[j] && sY[j] < tst && sY[j] <= bestY) {
+          bestY = sY[j];
+          bestHS = sHS[j];
+          bestRgb = srgb[j];
+          any = true;
+        }
       }
     }
     uint32_t srec = 0u, scount = 0u;
     if (any) {
-      scount = (uint32_t)fminf(fmaxf(ceilf(bestHS - 0.5f), 0.f), halfH);
+      scount = (uint32_t)__builtin_amdgcn_fmed3f(ceilf(bestHS - 0.5f), 0.f, halfH);
       srec = bestRgb | (scount << 24);
     }
     // span record: wall colour with the covered half-height (wall or sprite),
     // sprite colour with the sprite's half-height
-    lcol[2 * col] = wc | ((wcount > scount ? wcount : scount) << 24);
-    lcol[2 * col + 1] = srec;
+    *reinterpret_cast<u32x2*>(lcol + 2 * col) = u32x2{wc | ((wcount > scount ? wcount : scount) << 24), srec};
     if (io.dbg) {
       ColDbg* d = reinterpret_cast<ColDbg*>(io.dbg) + (int64_t)env * io.dbg_stride + col;
-      *d = ColDbg{hit, side, tst, cell};
+      *d = ColDbg{hit, xface ? 0 : 1, tst, cell};
     }
   }
   wave_sync();
@@ -857,7 +875,8 @@ __device__ void fill_frame_f(const uint32_t* lcol, const uint32_t* lcvt, uint8_t
   }
 }
 
-template <int FMT>
+// BOUND: keep at most two row pairs of the wave's stores in flight (see kWaitTwoPairs).
+template <int FMT, bool BOUND>
 __device__ void fill_frame(const uint32_t* lcol, const uint32_t* lcvt, uint8_t* base, int W, int H, int lane,
                            int nt, int part = 0, int parts = 1) {
   if constexpr (FMT != 0) {
@@ -884,7 +903,7 @@ __device__ void fill_frame(const uint32_t* lcol, const uint32_t* lcvt, uint8_t* 
     const uint32_t dii = (uint32_t)pdi * kRowStep;
     for (; i < H2; i += pdi) {
       emit_pair(g, (uint32_t)i, ii, up, dn, nt);
-      __builtin_amdgcn_s_waitcnt(kWaitTwoPairs);
+      if (BOUND) __builtin_amdgcn_s_waitcnt(kWaitTwoPairs);
       ii += dii;
       up -= step;
       dn += step;
@@ -916,13 +935,16 @@ struct EnvIn {
   int goal, door, key, dec0, dec1, nd;
   int ak0, ak1, ak2;  // ASCII maps: key tiles (constant per env)
   uint64_t seed;
-  double sn, cs;      // sine and cosine of th, in double
+  uint32_t act;       // per-step forms: this step's action
+  double sn, cs;      // fused form: sine and cosine of th, in double
   uint32_t map[kMapWords];
 };
 
+// act: the step's actions, loaded beside the state (nullable).
 template <int MAXN>
-__device__ __forceinline__ void load_env(const DevState& S, int env, int lane, EnvIn<MAXN>& in) {
+__device__ __forceinline__ void load_env(const DevState& S, const uint8_t* act, int env, int lane, EnvIn<MAXN>& in) {
   in.env = env;
+  in.act = act ? act[env] : 0u;
   in.cf = S.uniform ? S.ucfg : S.cfgs[S.cfg_idx[env]];
   const int NN = in.cf.side * in.cf.side;
   const uint8_t* mp = S.uniform ? S.maps + (int64_t)env * S.map_stride : S.maps + S.map_off[env];
@@ -949,7 +971,6 @@ __device__ __forceinline__ void load_env(const DevState& S, int env, int lane, E
   in.ak0 = S.akey[3 * env];
   in.ak1 = S.akey[3 * env + 1];
   in.ak2 = S.akey[3 * env + 2];
-  sincos((double)in.th, &in.sn, &in.cs);
 }
 
 // Bit mask of the map's locked doors of colour c (door type c), gathered by
@@ -962,129 +983,149 @@ __device__ uint32_t locked_doors_of(const uint8_t* lmap, int NN, uint32_t c, int
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m |= (uint32_t)__shfl_xor((int)m, off, 64);
-  return m;
+  return uniform_u(m);
 }
 
-// Copies the env's layout words from registers into the wave's LDS map.  The
-// LDS map is read-only afterwards (the shut door is tested separately), so a
-// wave that keeps one env for several steps stages it once.
+// Copies the env's layout words from registers into the wave's LDS map and puts
+// the guards around it.  The LDS map is read-only afterwards (the shut door is
+// tested separately), so a wave that keeps one env for several steps stages it
+// once.
 template <int MAXN>
 __device__ __forceinline__ void stage_map(const EnvIn<MAXN>& in, int lane, uint8_t* lmap) {
-  const int NN = in.cf.side * in.cf.side;
+  constexpr uint32_t kBlock = 0x01010101u;
+  constexpr int kGuard = guard_bytes(MAXN) / 4;  // words
+  const int NN = in.cf.side * in.cf.side, part = NN & 3;
   uint32_t* lm32 = reinterpret_cast<uint32_t*>(lmap);
 #pragma unroll
   for (int k = 0; k < EnvIn<MAXN>::kMapWords; ++k) {
     const int i = lane + 64 * k;
-    if (i < ((NN + 3) >> 2)) lm32[i] = in.map[k];
+    // the word that the map ends in, if any, ends with the guard
+    if (i < ((NN + 3) >> 2)) {
+      const uint32_t tail = part && i == (NN >> 2) ? ~0u << (8 * part) : 0u;
+      lm32[i] = (in.map[k] & ~tail) | (kBlock & tail);
+    }
+  }
+  if (lane < kGuard) {
+    lm32[lane - kGuard] = kBlock;
+    lm32[((NN + 3) >> 2) + lane] = kBlock;
   }
 }
 
 // Step, reset and column cast of one env from its loaded inputs: LDS and
 // registers only, no global stores (so a wave doing only this never waits on
 // outstanding stores).  All lanes run the uniform parts redundantly.
-// STAGE: copy the layout into LDS first (else it is already there).
-// action < 0: read this env's action from io.act.
+// STAGE: a per-step form, which copies the layout into LDS and computes the
+// heading's sine and cosine (the fused form has staged the layout and carries
+// both in its inputs).
+// part, casters: `casters` waves run the same step, each on its own LDS map, and
+// cast every casters-th block of 64 columns into the shared records.
 template <int MAXN, bool STAGE, bool ASC>
-__device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevIo& io, int action,
-                            int lane, uint8_t* lmap, const uint32_t* lclr, uint32_t* lcol, EnvOut& o) {
+__device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
+                            int lane, uint8_t* lmap, const uint32_t* lclr, uint32_t* lcol, EnvOut& o,
+                            int part = 0, int casters = 1) {
+#pragma clang fp contract(off)
   const DevCfg& cf = in.cf;
   const int env = in.env;
   const int N = cf.side;
+  const TileDiv td(N);
   if (STAGE) stage_map<MAXN>(in, lane, lmap);
   float x = in.x, y = in.y, th = in.th;
   uint32_t t = in.t, ep = in.ep;
   int goal = in.goal, door = in.door, key = in.key;
   int dec0 = in.dec0, dec1 = in.dec1;
-  uint32_t fl = in.fl;
+  uint32_t fl = uniform_u(in.fl);
   uint32_t doors = in.doors;
-  int nd = in.nd;
+  int nd = (int)uniform_u((uint32_t)in.nd);
+  a = (int)uniform_u((uint32_t)a);
   const uint64_t seed = in.seed;
   wave_sync();
 
+  // Every value here is uniform across the wave.  The branches ask ballots, so
+  // they stay scalar.  (Moving the state itself into scalar registers as well
+  // took 40 lane registers off, but made a step of the fused rollout 3% and a
+  // reset of the 32-side key-door envs 20% slower: the scalar registers spill.)
   const int mode = io.mode;
   float reward = 0.f;
   uint32_t ev = 0;
   bool done = false;
-  // sine and cosine of the heading in double (from the env's inputs; they
-  // are recomputed only when the heading changes)
+  // Sine and cosine of the heading in double, once per heading: an action
+  // either turns (nothing moves, and only the new heading's are needed) or
+  // keeps the heading.
   double dsn = in.sn, dcs = in.cs;
-  const float sn = (float)dsn, cs = (float)dcs;
   bool heading_changed = false;
   uint32_t prev = (uint32_t)cf.n_actions;
+  const int turn_l = cf.n_actions == 4 ? 2 : 4;
+  const bool turns = mode == MODE_STEP && a >= turn_l && a < cf.n_actions && cf.turn != 0.f;
+  if (turns) {
+    float t2 = th + (a == turn_l ? -cf.turn : cf.turn);
+    if (t2 < 0.f) t2 += kTwoPiF;
+    else if (t2 >= kTwoPiF) t2 -= kTwoPiF;
+    th = t2;
+    heading_changed = true;
+  } else if (STAGE && mode != MODE_RESET) {
+    sincos((double)th, &dsn, &dcs);
+  }
   if (mode == MODE_STEP) {
-    const int a = action >= 0 ? action : io.act[env];
-    if (a < cf.n_actions) prev = (uint32_t)a;
-    float mvx = 0.f, mvy = 0.f, dth = 0.f;
-    if (a >= cf.n_actions) {
-      ev |= EV_INVALID;
-    } else if (cf.n_actions == 4) {
-      if (a == 0) { mvx = cs; mvy = sn; }
-      else if (a == 1) { mvx = -cs; mvy = -sn; }
-      else if (a == 2) dth = -cf.turn;
-      else dth = cf.turn;
-    } else {
-      if (a == 0) { mvx = cs; mvy = sn; }
-      else if (a == 1) { mvx = -cs; mvy = -sn; }
-      else if (a == 2) { mvx = sn; mvy = -cs; }
-      else if (a == 3) { mvx = -sn; mvy = cs; }
-      else if (a == 4) dth = -cf.turn;
-      else dth = cf.turn;
+    if (a >= cf.n_actions) ev |= EV_INVALID;
+    else prev = (uint32_t)a;
+    if (a < turn_l) {
+      const float sn = (float)dsn, cs = (float)dcs;
+      const float vx = a < 2 ? cs : sn, vy = a < 2 ? sn : cs;
+      const bool negx = a == 1 || a == 3, negy = a == 1 || a == 2;
+      const float mx = cf.move * (negx ? -vx : vx), my = cf.move * (negy ? -vy : vy);
+      const bool dclosed = door >= 0 && !(fl & FL_DOOR_OPEN);
+      // x first, then y from the new x: the three tiles either test can ask for
+      // are read together
+      const float nx = x + mx, ny = y + my;
+      const int tx0 = (int)floorf(x), ty0 = (int)floorf(y), tx1 = (int)floorf(nx), ty1 = (int)floorf(ny);
+      auto tile = [&](int tx, int ty) -> uint32_t {
+        const bool in_map = (unsigned)tx < (unsigned)N && (unsigned)ty < (unsigned)N;
+        return lmap[in_map ? ty * N + tx : -1];  // off the map: a guard
+      };
+      const uint32_t v10 = tile(tx1, ty0), v01 = tile(tx0, ty1), v11 = tile(tx1, ty1);
+      auto blocks = [&](uint32_t v, int tx, int ty) -> bool {
+        if (ASC && (v & kTileDoor)) return !((doors >> (v & 15u)) & 1u);  // map door: shut unless open
+        return (v & 0x0Fu) != 0u || (dclosed && ty * N + tx == door);
+      };
+      // ASCII maps: walking into a shut unlocked door opens it (the move is refused)
+      auto bump = [&](uint32_t v) {
+        v = uniform_u(v);
+        const uint32_t type = (v >> 4) & 7u;
+        if ((v & kTileDoor) && (type == kDoorBlueUnlocked || type == kDoorYellowUnlocked) &&
+            !((doors >> (v & 15u)) & 1u)) {
+          doors |= 1u << (v & 15u);
+          ev |= EV_DOOR;
+        }
+      };
+      bool moved = false;
+      if (wave_any(mx != 0.f)) {
+        if (!wave_any(blocks(v10, tx1, ty0))) {
+          x = nx;
+          moved = true;
+        } else {
+          ev |= EV_BLOCKED_X;
+          if (ASC) bump(v10);
+        }
+      }
+      if (wave_any(my != 0.f)) {
+        const uint32_t v = moved ? v11 : v01;
+        if (!wave_any(blocks(v, moved ? tx1 : tx0, ty1))) {
+          y = ny;
+        } else {
+          ev |= EV_BLOCKED_Y;
+          if (ASC) bump(v);
+        }
+      }
     }
-    if (dth != 0.f) {
-      float t2 = th + dth;
-      if (t2 < 0.f) t2 += kTwoPiF;
-      else if (t2 >= kTwoPiF) t2 -= kTwoPiF;
-      th = t2;
-      heading_changed = true;
-    }
-    const float mx = cf.move * mvx, my = cf.move * mvy;
-    const bool dclosed = door >= 0 && !(fl & FL_DOOR_OPEN);
-    auto blocks = [&](int tx, int ty) -> bool {
-      if ((unsigned)tx >= (unsigned)N || (unsigned)ty >= (unsigned)N) return true;
-      const int id = ty * N + tx;
-      const uint32_t v = lmap[id];
-      if (ASC && (v & kTileDoor)) return !((doors >> (v & 15u)) & 1u);  // map door: shut unless open
-      return (v & 0x0Fu) != 0u || (dclosed && id == door);
+    auto near_tile = [&](int id) -> bool {
+      const float dx = x - ((float)td.col(id) + 0.5f);
+      const float dy = y - ((float)td.row(id) + 0.5f);
+      return wave_any(fmaf(dx, dx, dy * dy) < cf.pr2);
     };
-    // ASCII maps: walking into a shut unlocked door opens it (the move is refused)
-    auto bump = [&](int tx, int ty) {
-      if ((unsigned)tx >= (unsigned)N || (unsigned)ty >= (unsigned)N) return;
-      const uint32_t v = lmap[ty * N + tx];
-      const uint32_t type = (v >> 4) & 7u;
-      if ((v & kTileDoor) && (type == kDoorBlueUnlocked || type == kDoorYellowUnlocked) &&
-          !((doors >> (v & 15u)) & 1u)) {
-        doors |= 1u << (v & 15u);
-        ev |= EV_DOOR;
-      }
-    };
-    if (mx != 0.f) {
-      const float nx = x + mx;
-      const int tx = (int)floorf(nx), ty = (int)floorf(y);
-      if (!blocks(tx, ty)) {
-        x = nx;
-      } else {
-        ev |= EV_BLOCKED_X;
-        if (ASC) bump(tx, ty);
-      }
-    }
-    if (my != 0.f) {
-      const float ny = y + my;
-      const int tx = (int)floorf(x), ty = (int)floorf(ny);
-      if (!blocks(tx, ty)) {
-        y = ny;
-      } else {
-        ev |= EV_BLOCKED_Y;
-        if (ASC) bump(tx, ty);
-      }
-    }
-    if (key >= 0 && !(fl & FL_KEY)) {
-      const float dx = x - ((float)(key % N) + 0.5f);
-      const float dy = y - ((float)(key / N) + 0.5f);
-      if (dx * dx + dy * dy < cf.pr2) {
-        fl |= FL_KEY | FL_DOOR_OPEN;
-        reward += cf.r_key;
-        ev |= EV_KEY;
-      }
+    if (key >= 0 && !(fl & FL_KEY) && near_tile(key)) {
+      fl |= FL_KEY | FL_DOOR_OPEN;
+      reward += cf.r_key;
+      ev |= EV_KEY;
     }
     if (ASC && cf.ascii) {
       // ASCII maps: picking up the key of colour c opens every locked door of colour c
@@ -1092,9 +1133,7 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevI
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         if (ak[c] < 0 || (fl & (FL_AKEY0 << c))) continue;
-        const float dx = x - ((float)(ak[c] % N) + 0.5f);
-        const float dy = y - ((float)(ak[c] / N) + 0.5f);
-        if (dx * dx + dy * dy < cf.pr2) {
+        if (near_tile(ak[c])) {
           fl |= FL_AKEY0 << c;
           reward += cf.r_key;
           ev |= EV_KEY;
@@ -1105,7 +1144,7 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevI
       }
     }
     bool term = false;
-    if (goal >= 0 && (int)floorf(x) == goal % N && (int)floorf(y) == goal / N) {
+    if (goal >= 0 && wave_any((int)floorf(x) == td.col(goal) && (int)floorf(y) == td.row(goal))) {
       reward += cf.r_goal;
       term = true;
       ev |= EV_GOAL;
@@ -1118,9 +1157,11 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevI
   }
   if (mode == MODE_RESET || done) {
     const uint32_t e = (mode == MODE_RESET) ? 0u : ep + 1u;
-    // (the span records of the previous frame are spent: their LDS is scratch here)
-    const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, uint32_t>(cf, lmap, lcol, seed, e, lane)
-                                            : episode_reset<ASC, uint64_t>(cf, lmap, lcol, seed, e, lane);
+    // the LDS of the records that this wave is about to write is scratch here
+    // (where two waves cast, each has the half of its own 64 columns)
+    uint32_t* lbits = lcol + 128 * part;
+    const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, uint32_t>(cf, td, lmap, lbits, seed, e, lane)
+                                            : episode_reset<ASC, uint64_t>(cf, td, lmap, lbits, seed, e, lane);
     x = n.x;
     y = n.y;
     th = n.th;
@@ -1139,8 +1180,8 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevState& S, const DevI
   }
   if (heading_changed) sincos((double)th, &dsn, &dcs);
   if (io.obs || io.dbg)
-    render_columns<ASC>(cf, io, env, lane, lmap, lclr, lcol, x, y, dsn, dcs, goal, door, key, fl, nd, dec0, dec1,
-                   doors, in.ak0, in.ak1, in.ak2);
+    render_columns<ASC>(cf, td, io, env, lane + 64 * part, 64 * casters, lmap, lclr, lcol, x, y, dsn, dcs, goal, door,
+                        key, fl, nd, dec0, dec1, doors, in.ak0, in.ak1, in.ak2);
   o.obs_off = 0;  // set by the caller (obs_off_of), outside any step loop
   o.env = env;
   o.W = cf.obs_w;
@@ -1198,20 +1239,36 @@ __device__ __forceinline__ int64_t obs_off_of(const DevState& S, int env) {
   return S.uniform ? (int64_t)env * S.obs_stride : S.obs_off[env];
 }
 
-// The whole per-env pipeline in one wave.
-// part / parts: this wave is one of `parts` waves sharing the env; each runs
-// the same step and cast, fills its share of the frame's row pairs, and only
-// part 0 writes the state and the step's outputs.
+// The whole per-env pipeline.
+// part / parts: this wave is one of `parts` waves of a workgroup that share the
+// env and its records `lcol`.  Wave 0 steps and casts (two waves do, half of the
+// columns each, where a row has more than one wave's 64), the others wait for
+// the records; then each fills its share of the frame's row pairs.  live: the
+// wave has an env (all waves meet at the barrier).  One wave writes a frame at
+// about 20 bytes a cycle, so a large frame is most of a small batch's step: 100
+// envs of 128 x 128 float32 frames take 23.3 us with one wave each and 12.7 us
+// with four, 256 of 64 x 64 12.0 and 10.4 us.
 template <int MAXN, bool ASC, int FMT>
 __device__ __forceinline__ void process_env(const DevState& S, const DevIo& io, int env, int lane, uint8_t* lmap,
                             const uint32_t* lclr, const uint32_t* lcvt, uint32_t* lcol, int part = 0,
-                            int parts = 1) {
-  EnvIn<MAXN> in;
-  load_env<MAXN>(S, env, lane, in);
-  EnvOut o;
-  produce_env<MAXN, true, ASC>(in, S, io, -1, lane, lmap, lclr, lcol, o);
+                            int parts = 1, bool live = true) {
+  EnvOut o{};
+  if (live) {
+    const DevCfg& cf = S.uniform ? S.ucfg : S.cfgs[S.cfg_idx[env]];
+    const int casters = parts > 1 && cf.obs_w > 64 ? 2 : 1;
+    if (part < casters) {
+      EnvIn<MAXN> in;
+      load_env<MAXN>(S, io.mode == MODE_STEP ? io.act : nullptr, env, lane, in);
+      produce_env<MAXN, true, ASC>(in, io, (int)in.act, lane, lmap, lclr, lcol, o, part, casters);
+    } else {
+      o.W = cf.obs_w;
+      o.H = cf.obs_h;
+    }
+  }
+  if (parts > 1) __syncthreads();
+  if (!live) return;
   o.obs_off = obs_off_of(S, env);
-  if (io.obs) fill_frame<FMT>(lcol, lcvt, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode, part, parts);
+  if (io.obs) fill_frame<FMT, false>(lcol, lcvt, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode, part, parts);
   if (part == 0) write_back(S, io, o, lane);
 }
 
@@ -1229,11 +1286,11 @@ __device__ __forceinline__ DevIo io_of(const DevIo& io, const RolloutDesc* rd, i
   return r;
 }
 
-// wpe waves per env (1, 2 or 4): consecutive waves share an env.
+// wpe waves per env (1, 2 or 4): consecutive waves of a workgroup share an env.
 template <int MAXN, int WPB, bool ASC, int FMT>
 __global__ __launch_bounds__(64 * WPB) void k_plain(DevState S, DevIo io0, const RolloutDesc* rd,
                                                     int t, int wpe) {
-  __shared__ __align__(16) uint8_t smap[WPB][MAXN * MAXN];
+  __shared__ __align__(16) uint8_t smap[WPB][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   __shared__ uint32_t scvt[FMT % 3 ? 256 : 1];
@@ -1241,9 +1298,10 @@ __global__ __launch_bounds__(64 * WPB) void k_plain(DevState S, DevIo io0, const
   const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
   const int gw = __builtin_amdgcn_readfirstlane((int)blockIdx.x * WPB + w);
   const int env = gw / wpe, part = gw - env * wpe;
-  if (env >= S.n) return;
+  if (wpe == 1 && env >= S.n) return;
   const DevIo io = io_of(io0, rd, t);
-  process_env<MAXN, ASC, FMT>(S, io, env, lane, smap[w], sclr, scvt, scol[w], part, wpe);
+  process_env<MAXN, ASC, FMT>(S, io, env, lane, smap[w] + guard_bytes(MAXN), sclr, scvt, scol[w - part], part, wpe,
+                              env < S.n);
 }
 
 // Work distribution of the persistent forms (word 0 of a queue's line counts
@@ -1318,7 +1376,7 @@ __device__ __forceinline__ void queue_drain(const QueueView& v, int lane, F&& f)
 template <int WPB, bool ASC>
 __global__ __launch_bounds__(64 * WPB) void k_persist(DevState S, DevIo io0, const RolloutDesc* rd,
                                                       int t, uint32_t seq) {
-  __shared__ __align__(16) uint8_t smap[WPB][kMaxSide * kMaxSide];
+  __shared__ __align__(16) uint8_t smap[WPB][map_slice(kMaxSide)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   stage_colors(sclr);
@@ -1327,7 +1385,7 @@ __global__ __launch_bounds__(64 * WPB) void k_persist(DevState S, DevIo io0, con
   const QueueView v = queue_view<WPB>(S.queues, seq, S.n, w, lane);
   queue_drain(v, lane, [&](int pos) {
     const int env = __builtin_amdgcn_readfirstlane(S.order[pos]);
-    process_env<kMaxSide, ASC, 0>(S, io, env, lane, smap[w], sclr, nullptr, scol[w]);
+    process_env<kMaxSide, ASC, 0>(S, io, env, lane, smap[w] + guard_bytes(kMaxSide), sclr, nullptr, scol[w]);
   });
 }
 
@@ -1336,7 +1394,7 @@ template <int WPB>
 __global__ __launch_bounds__(64 * WPB) void k_serve(const DevState* states, const DevIo* ios,
                                                     const ServeItem* items, int n_items,
                                                     uint32_t* queues, uint32_t seq) {
-  __shared__ __align__(16) uint8_t smap[WPB][kMaxSide * kMaxSide];
+  __shared__ __align__(16) uint8_t smap[WPB][map_slice(kMaxSide)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   stage_colors(sclr);
@@ -1348,7 +1406,7 @@ __global__ __launch_bounds__(64 * WPB) void k_serve(const DevState* states, cons
     // fields are read from the descriptors where they are used (scalar loads)
     const DevState& S = states[d];
     const DevIo& io = ios[d];
-    process_env<kMaxSide, true, 0>(S, io, env, lane, smap[w], sclr, nullptr, scol[w]);
+    process_env<kMaxSide, true, 0>(S, io, env, lane, smap[w] + guard_bytes(kMaxSide), sclr, nullptr, scol[w]);
   });
 }
 
@@ -1363,7 +1421,7 @@ __global__ __launch_bounds__(64 * WPB) void k_serve(const DevState* states, cons
 template <int MAXN, int P, bool ASC>
 __global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const RolloutDesc* rd,
                                                   int t) {
-  __shared__ __align__(16) uint8_t smap[P][MAXN * MAXN];
+  __shared__ __align__(16) uint8_t smap[P][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[P][2][2 * kMaxW];
   __shared__ EnvOut sout[P][2];
   __shared__ uint32_t sclr[kColorWords];
@@ -1377,16 +1435,16 @@ __global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const R
   const int lead = (int)blockIdx.x * P;  // the workgroup's pair with the most items
   const int rounds = S.n > lead ? (S.n - lead + pairs - 1) / pairs : 0;
   EnvIn<MAXN> cur, nxt;
-  if (!writer && gp < S.n) load_env<MAXN>(S, __builtin_amdgcn_readfirstlane(S.order[gp]), lane, cur);
+  if (!writer && gp < S.n) load_env<MAXN>(S, io.act, __builtin_amdgcn_readfirstlane(S.order[gp]), lane, cur);
   for (int k = 0; k <= rounds; ++k) {
     const int b = k & 1;
     if (!writer) {
       const int item = gp + k * pairs;
       if (k < rounds && item < S.n) {
         const int nitem = item + pairs;
-        if (nitem < S.n) load_env<MAXN>(S, __builtin_amdgcn_readfirstlane(S.order[nitem]), lane, nxt);
+        if (nitem < S.n) load_env<MAXN>(S, io.act, __builtin_amdgcn_readfirstlane(S.order[nitem]), lane, nxt);
         EnvOut o;
-        produce_env<MAXN, true, ASC>(cur, S, io, -1, lane, smap[pair], sclr, scol[pair][b], o);
+        produce_env<MAXN, true, ASC>(cur, io, (int)cur.act, lane, smap[pair] + guard_bytes(MAXN), sclr, scol[pair][b], o);
         o.obs_off = obs_off_of(S, o.env);
         if (lane == 0) sout[pair][b] = o;
         cur = nxt;
@@ -1396,7 +1454,7 @@ __global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const R
     } else if (k > 0) {
       const EnvOut o = sout[pair][b ^ 1];
       if (o.env >= 0) {
-        fill_frame<0>(scol[pair][b ^ 1], nullptr, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode);
+        fill_frame<0, true>(scol[pair][b ^ 1], nullptr, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode);
         write_back(S, io, o, lane);
       }
     }
@@ -1404,75 +1462,66 @@ __global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const R
   }
 }
 
-// One env's fused rollout: the wave carries the env through all T steps with
-// the state in registers and its layout staged once in LDS, loading the env's
-// actions 128 steps at a time.  Inside the step loop the wave issues no global
-// loads, so its frame stores never stall it, and waves drift out of phase: one
-// wave's casting overlaps another's stores.  Per step the results are those of
-// a single-step launch; the state is written back once, after the last step.
-template <int MAXN, bool ASC, int FMT>
-__device__ __forceinline__ void roll_env(const DevState& S, int env, int lane, uint8_t* lmap, const uint32_t* lclr,
-                                         const uint32_t* lcvt, uint32_t* lcol, const uint8_t* act, uint8_t* obs,
-                                         int64_t obs_stride, float* rew, uint8_t* dn, uint8_t* prv, int T,
-                                         int store_mode, const DevIo& io, int part = 0, int parts = 1) {
-  const int64_t n = S.n;
+// Buffers of a fused rollout.
+struct RollIo {
+  const uint8_t* act;
+  uint8_t* obs;
+  int64_t obs_stride;
+  float* rew;
+  uint8_t* dn;
+  uint8_t* prv;
+  int T, store_mode;
+};
+
+// An env carried through a fused rollout: the state in registers (the pose and
+// its sine and cosine in lane registers, the rest in scalar ones), the layout in
+// the wave's LDS.
+template <int MAXN>
+struct Carried {
   EnvIn<MAXN> in;
-  load_env<MAXN>(S, env, lane, in);
-  stage_map<MAXN>(in, lane, lmap);
-  const int64_t obs_off = obs_off_of(S, env);
   uint32_t n_invalid = 0, last_ev = 0;
-  for (int t0 = 0; t0 < T; t0 += 128) {
-    // lane l holds the actions of steps t0 + l and t0 + 64 + l
-    const int s0 = t0 + lane, s1 = t0 + 64 + lane;
-    const uint32_t a0 = s0 < T ? act[(int64_t)s0 * n + env] : 0u;
-    const uint32_t a1 = s1 < T ? act[(int64_t)s1 * n + env] : 0u;
-    const int tend = T - t0 < 128 ? T - t0 : 128;
-    for (int k = 0; k < tend; ++k) {
-      // (& 0xFF: the action is a byte, so produce_env's load path for a
-      // negative action folds away and the step loop issues no load)
-      // Wait for this wave's previous frame stores before the next step: a
-      // wave then has at most one frame's stores in flight.  Measured on the
-      // 4096-env workload this bound keeps the HBM write stream more
-      // efficient than letting stores of many steps pile up (and the casting
-      // of the other waves still overlaps them).  vmcnt 0, other counters
-      // untouched.
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      const int a = __shfl((int)(k < 64 ? a0 : a1), k & 63, 64) & 0xFF;
-      // an opaque copy of the lane id keeps the per-column set-up inside the
-      // loop instead of hoisted out of it and held live across all steps
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      EnvOut o;
-      produce_env<MAXN, false, ASC>(in, S, io, a, ln, lmap, lclr, lcol, o);
-      const int t = t0 + k;
-      fill_frame<FMT>(lcol, lcvt, obs + (int64_t)t * obs_stride + obs_off, o.W, o.H, ln, store_mode, part, parts);
-      if (lane == 0 && part == 0) {
-        rew[(int64_t)t * n + env] = o.reward;
-        dn[(int64_t)t * n + env] = (uint8_t)o.done;
-        if (prv) prv[(int64_t)t * n + env] = (uint8_t)o.prev;
-      }
-      // the carried state is uniform across the wave: keep it in scalar registers
-      const uint32_t ev = uniform_u(o.ev);
-      n_invalid += (ev & EV_INVALID) ? 1u : 0u;
-      last_ev = ev;
-      in.x = uniform_f(o.x);
-      in.y = uniform_f(o.y);
-      in.th = uniform_f(o.th);
-      in.t = uniform_u(o.t);
-      in.ep = uniform_u(o.ep);
-      in.fl = uniform_u(o.fl);
-      in.nd = (int)uniform_u(o.nd);
-      in.goal = (int)uniform_u((uint32_t)o.goal);
-      in.door = (int)uniform_u((uint32_t)o.door);
-      in.key = (int)uniform_u((uint32_t)o.key);
-      in.dec0 = (int)uniform_u((uint32_t)o.dec0);
-      in.dec1 = (int)uniform_u((uint32_t)o.dec1);
-      in.doors = uniform_u(o.doors);
-      in.sn = uniform_d(o.sn);
-      in.cs = uniform_d(o.cs);
-    }
+  uint32_t a0 = 0, a1 = 0;  // lane l: the actions of steps t0 + l and t0 + 64 + l of a block of 128
+
+  __device__ __forceinline__ void open(const DevState& S, int env, int lane, uint8_t* lmap) {
+    load_env<MAXN>(S, nullptr, env, lane, in);
+    sincos((double)in.th, &in.sn, &in.cs);
+    stage_map<MAXN>(in, lane, lmap);
   }
-  if (lane == 0 && part == 0 && T > 0) {
+  __device__ __forceinline__ void load_actions(int n, const RollIo& r, int t0, int lane) {
+    const int s0 = t0 + lane, s1 = t0 + 64 + lane;
+    a0 = s0 < r.T ? r.act[(int64_t)s0 * n + in.env] : 0u;
+    a1 = s1 < r.T ? r.act[(int64_t)s1 * n + in.env] : 0u;
+  }
+  __device__ __forceinline__ int action(int k) const { return (int)lane_value(k < 64 ? a0 : a1, k); }
+  // Step t's reward, done and previous action, and the state for the next step.
+  __device__ __forceinline__ void take(int n, const RollIo& r, const EnvOut& o, int t, bool store) {
+    if (store) {
+      const int64_t at = (int64_t)t * n + in.env;
+      r.rew[at] = o.reward;
+      r.dn[at] = (uint8_t)o.done;
+      if (r.prv) r.prv[at] = (uint8_t)o.prev;
+    }
+    n_invalid += (o.ev & EV_INVALID) ? 1u : 0u;
+    last_ev = o.ev;
+    in.x = o.x;
+    in.y = o.y;
+    in.th = o.th;
+    in.t = o.t;
+    in.ep = o.ep;
+    in.fl = o.fl;
+    in.nd = (int)o.nd;
+    in.goal = o.goal;
+    in.door = o.door;
+    in.key = o.key;
+    in.dec0 = o.dec0;
+    in.dec1 = o.dec1;
+    in.doors = o.doors;
+    in.sn = o.sn;
+    in.cs = o.cs;
+  }
+  // Lane 0 of the env's first wave, after the last step.
+  __device__ __forceinline__ void close(const DevState& S) const {
+    const int env = in.env;
     S.x[env] = in.x;
     S.y[env] = in.y;
     S.th[env] = in.th;
@@ -1489,32 +1538,147 @@ __device__ __forceinline__ void roll_env(const DevState& S, int env, int lane, u
     S.doors[env] = in.doors;
     if (n_invalid) S.invalid[env] += n_invalid;
   }
+};
+
+// The kernel's first argument, read anew from the argument segment.  A fused
+// rollout needs the state's 25 addresses before and after its step loop only;
+// held across the loop they would fill the scalar registers, and the loop would
+// spend its time moving spilled ones in and out of lanes.
+__device__ __forceinline__ const DevState& kernarg_state() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const DevState*)(const __attribute__((address_space(4))) DevState*)p;
+}
+
+__device__ __forceinline__ DevIo roll_step_io(const RollIo& r) {
+  DevIo io{};
+  io.obs = r.obs;
+  io.mode = MODE_STEP;
+  io.store_mode = r.store_mode;
+  return io;
+}
+
+// One env's fused rollout: the wave carries the env through all T steps with
+// the state in registers and its layout staged once in LDS, loading the env's
+// actions 128 steps at a time.  Inside the step loop the wave issues no global
+// loads, so its frame stores never stall it, and waves drift out of phase: one
+// wave's casting overlaps another's stores.  Per step the results are those of
+// a single-step launch; the state is written back once, after the last step.
+template <int MAXN, bool ASC, int FMT>
+__device__ __forceinline__ void roll_env(int n, int env, int lane, uint8_t* lmap, const uint32_t* lclr,
+                                         const uint32_t* lcvt, uint32_t* lcol, const RollIo& r) {
+  const DevIo io = roll_step_io(r);
+  Carried<MAXN> c;
+  int64_t obs_off;
+  {
+    const DevState& S = kernarg_state();
+    c.open(S, env, lane, lmap);
+    obs_off = obs_off_of(S, env);
+  }
+  for (int t0 = 0; t0 < r.T; t0 += 128) {
+    c.load_actions(n, r, t0, lane);
+    const int tend = r.T - t0 < 128 ? r.T - t0 : 128;
+    for (int k = 0; k < tend; ++k) {
+      // Wait for this wave's previous frame stores before the next step: a
+      // wave then has at most one frame's stores in flight.  Measured on the
+      // 4096-env workload this bound keeps the HBM write stream more
+      // efficient than letting stores of many steps pile up (and the casting
+      // of the other waves still overlaps them).  vmcnt 0, other counters
+      // untouched.
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      // an opaque copy of the lane id keeps the per-column set-up inside the
+      // loop instead of hoisted out of it and held live across all steps
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      EnvOut o;
+      produce_env<MAXN, false, ASC>(c.in, io, c.action(k), ln, lmap, lclr, lcol, o);
+      const int t = t0 + k;
+      fill_frame<FMT, true>(lcol, lcvt, r.obs + (int64_t)t * r.obs_stride + obs_off, o.W, o.H, ln, r.store_mode);
+      c.take(n, r, o, t, lane == 0);
+    }
+  }
+  if (lane == 0 && r.T > 0) c.close(kernarg_state());
 }
 
 // Fused rollout: one launch for T steps of every env.  Waves take envs by a
-// static stride over the work order (costliest first); wpe consecutive waves
-// share an env (each fills its share of the row pairs).
+// static stride over the work order (costliest first).
 template <int MAXN, int WPB, bool ASC, int FMT>
-__global__ __launch_bounds__(64 * WPB) void k_roll(DevState S, const uint8_t* act, uint8_t* obs,
-                                                   int64_t obs_stride, float* rew, uint8_t* dn,
-                                                   uint8_t* prv, int T, int store_mode, int wpe) {
-  __shared__ __align__(16) uint8_t smap[WPB][MAXN * MAXN];
+__global__ __launch_bounds__(64 * WPB) void k_roll(DevState S, RollIo r) {
+  __shared__ __align__(16) uint8_t smap[WPB][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   __shared__ uint32_t scvt[FMT % 3 ? 256 : 1];
   stage_tables<FMT>(sclr, scvt);
   const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  const int gw = __builtin_amdgcn_readfirstlane((int)blockIdx.x * WPB + w);
-  const int first = gw / wpe, part = gw - first * wpe;
-  const int stride = (int)gridDim.x * WPB / wpe;
-  DevIo io{};
-  io.obs = obs;
-  io.mode = MODE_STEP;
-  io.store_mode = store_mode;
+  const int first = __builtin_amdgcn_readfirstlane((int)blockIdx.x * WPB + w);
+  const int stride = (int)gridDim.x * WPB;
   for (int item = first; item < S.n; item += stride) {
-    const int env = __builtin_amdgcn_readfirstlane(S.order[item]);
-    roll_env<MAXN, ASC, FMT>(S, env, lane, smap[w], sclr, scvt, scol[w], act, obs, obs_stride, rew, dn, prv, T,
-                             store_mode, io, part, wpe);
+    const int env = __builtin_amdgcn_readfirstlane(kernarg_state().order[item]);
+    roll_env<MAXN, ASC, FMT>(S.n, env, lane, smap[w] + guard_bytes(MAXN), sclr, scvt, scol[w], r);
+  }
+}
+
+// Fused rollout with several waves per env (wpe 2 or 4), for batches that leave
+// the chip idle, where a step costs its latency: one wave steps and casts step
+// t (two waves do, half of the columns each, where four share an env whose rows
+// have more than 64 columns) while the others write step t - 1's frame.  The
+// records alternate between two LDS buffers, one workgroup barrier per step.
+// A workgroup's 4 waves hold 4 / wpe envs; all of them meet at every barrier.
+// 64 steps of 512 envs (25-side, 64 x 64): 219 us with one wave per env, 161 with
+// two and 169 with four (every wave stepping and casting for itself: 222, 223).
+template <int MAXN, bool ASC, int FMT>
+__global__ __launch_bounds__(256) void k_roll_split(DevState S, RollIo r, int wpe) {
+  __shared__ __align__(16) uint8_t smap[4][map_slice(MAXN)];
+  __shared__ __align__(16) uint32_t scol[2][2][2 * kMaxW];
+  __shared__ uint32_t sclr[kColorWords];
+  __shared__ uint32_t scvt[FMT % 3 ? 256 : 1];
+  stage_tables<FMT>(sclr, scvt);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+  const int slots = 4 / wpe, slot = w / wpe, part = w - slot * wpe;
+  const DevIo io = roll_step_io(r);
+  const int n = S.n;
+  for (int first = (int)blockIdx.x * slots; first < n; first += (int)gridDim.x * slots) {
+    // a slot past the last env runs that env once more and stores nothing
+    const bool live = first + slot < n;
+    int env, W, H;
+    int64_t obs_off;
+    {
+      const DevState& Q = kernarg_state();
+      env = __builtin_amdgcn_readfirstlane(Q.order[live ? first + slot : n - 1]);
+      const DevCfg& cf = Q.uniform ? Q.ucfg : Q.cfgs[Q.cfg_idx[env]];
+      W = (int)uniform_u((uint32_t)cf.obs_w);
+      H = (int)uniform_u((uint32_t)cf.obs_h);
+      obs_off = obs_off_of(Q, env);
+    }
+    const int casters = wpe == 4 && W > 64 ? 2 : 1;
+    if (part < casters) {
+      Carried<MAXN> c;
+      c.open(kernarg_state(), env, lane, smap[w] + guard_bytes(MAXN));
+      const bool store = live && lane == 0 && part == 0;
+      for (int t = 0; t < r.T; ++t) {
+        if ((t & 127) == 0) c.load_actions(n, r, t, lane);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        EnvOut o;
+        produce_env<MAXN, false, ASC>(c.in, io, c.action(t & 127), ln, smap[w] + guard_bytes(MAXN), sclr,
+                                      scol[slot][t & 1], o, part, casters);
+        c.take(n, r, o, t, store);
+        __syncthreads();
+      }
+      __syncthreads();  // the writers' last frame
+      if (store) c.close(kernarg_state());
+    } else {
+      uint8_t* at = r.obs + obs_off;
+      for (int t = 0; t < r.T; ++t) {
+        __syncthreads();  // step t's records are in buffer t & 1
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        if (live)
+          fill_frame<FMT, false>(scol[slot][t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, wpe - casters);
+        at += r.obs_stride;
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -1526,23 +1690,16 @@ __global__ __launch_bounds__(64 * WPB) void k_roll(DevState S, const uint8_t* ac
 // static stride leaves workgroups waiting on their slowest wave.  The queues
 // and counter sets are those of k_persist (one claim per env: chunk 1).
 template <int MAXN, int WPB, bool ASC>
-__global__ __launch_bounds__(64 * WPB) void k_proll(DevState S, const uint8_t* act, uint8_t* obs,
-                                                    int64_t obs_stride, float* rew, uint8_t* dn,
-                                                    uint8_t* prv, int T, int store_mode, uint32_t seq) {
-  __shared__ __align__(16) uint8_t smap[WPB][MAXN * MAXN];
+__global__ __launch_bounds__(64 * WPB) void k_proll(DevState S, RollIo r, uint32_t seq) {
+  __shared__ __align__(16) uint8_t smap[WPB][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   stage_colors(sclr);
   const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  DevIo io{};
-  io.obs = obs;
-  io.mode = MODE_STEP;
-  io.store_mode = store_mode;
   const QueueView v = queue_view<WPB>(S.queues, seq, S.n, w, lane, 1);
   queue_drain(v, lane, [&](int pos) {
-    const int env = __builtin_amdgcn_readfirstlane(S.order[pos]);
-    roll_env<MAXN, ASC, 0>(S, env, lane, smap[w], sclr, nullptr, scol[w], act, obs, obs_stride, rew, dn, prv, T,
-                           store_mode, io);
+    const int env = __builtin_amdgcn_readfirstlane(kernarg_state().order[pos]);
+    roll_env<MAXN, ASC, 0>(S.n, env, lane, smap[w] + guard_bytes(MAXN), sclr, nullptr, scol[w], r);
   });
 }
 
@@ -1599,32 +1756,30 @@ int launch_pipe_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, int
 }
 
 template <int MAXN, bool ASC, int FMT>
-int launch_roll_n(const DevState& s, const uint8_t* act, uint8_t* obs, int64_t obs_stride, float* rew,
-                  uint8_t* dn, uint8_t* pv, int T, int wpb, int groups, int nt, int wpe, hipStream_t st) {
-  if constexpr (FMT != 0) {
-    hipLaunchKernelGGL((k_roll<MAXN, kFmtWaves, ASC, FMT>), dim3(groups), dim3(64 * kFmtWaves), 0, st, s, act,
-                       obs, obs_stride, rew, dn, pv, T, nt, wpe);
-    return (int)hipGetLastError();
+int launch_roll_n(const DevState& s, const RollIo& r, int wpb, int groups, int wpe, hipStream_t st) {
+  if (wpe > 1) {
+    hipLaunchKernelGGL((k_roll_split<MAXN, ASC, FMT>), dim3(groups), dim3(256), 0, st, s, r, wpe);
+  } else if constexpr (FMT != 0) {
+    hipLaunchKernelGGL((k_roll<MAXN, kFmtWaves, ASC, FMT>), dim3(groups), dim3(64 * kFmtWaves), 0, st, s, r);
   } else {
     switch (wpb) {
-      case 1: hipLaunchKernelGGL((k_roll<MAXN, 1, ASC, 0>), dim3(groups), dim3(64), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, wpe); break;
-      case 2: hipLaunchKernelGGL((k_roll<MAXN, 2, ASC, 0>), dim3(groups), dim3(128), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, wpe); break;
-      case 4: hipLaunchKernelGGL((k_roll<MAXN, 4, ASC, 0>), dim3(groups), dim3(256), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, wpe); break;
-      case 8: hipLaunchKernelGGL((k_roll<MAXN, 8, ASC, 0>), dim3(groups), dim3(512), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, wpe); break;
+      case 1: hipLaunchKernelGGL((k_roll<MAXN, 1, ASC, 0>), dim3(groups), dim3(64), 0, st, s, r); break;
+      case 2: hipLaunchKernelGGL((k_roll<MAXN, 2, ASC, 0>), dim3(groups), dim3(128), 0, st, s, r); break;
+      case 4: hipLaunchKernelGGL((k_roll<MAXN, 4, ASC, 0>), dim3(groups), dim3(256), 0, st, s, r); break;
+      case 8: hipLaunchKernelGGL((k_roll<MAXN, 8, ASC, 0>), dim3(groups), dim3(512), 0, st, s, r); break;
       default: return -1;
     }
-    return (int)hipGetLastError();
   }
+  return (int)hipGetLastError();
 }
 
 template <int MAXN, bool ASC, int FMT>
-int launch_proll_n(const DevState& s, const uint8_t* act, uint8_t* obs, int64_t obs_stride, float* rew,
-                   uint8_t* dn, uint8_t* pv, int T, int wpb, int groups, int nt, uint32_t seq, hipStream_t st) {
+int launch_proll_n(const DevState& s, const RollIo& r, int wpb, int groups, uint32_t seq, hipStream_t st) {
   switch (wpb) {
-    case 1: hipLaunchKernelGGL((k_proll<MAXN, 1, ASC>), dim3(groups), dim3(64), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, seq); break;
-    case 2: hipLaunchKernelGGL((k_proll<MAXN, 2, ASC>), dim3(groups), dim3(128), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, seq); break;
-    case 4: hipLaunchKernelGGL((k_proll<MAXN, 4, ASC>), dim3(groups), dim3(256), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, seq); break;
-    case 8: hipLaunchKernelGGL((k_proll<MAXN, 8, ASC>), dim3(groups), dim3(512), 0, st, s, act, obs, obs_stride, rew, dn, pv, T, nt, seq); break;
+    case 1: hipLaunchKernelGGL((k_proll<MAXN, 1, ASC>), dim3(groups), dim3(64), 0, st, s, r, seq); break;
+    case 2: hipLaunchKernelGGL((k_proll<MAXN, 2, ASC>), dim3(groups), dim3(128), 0, st, s, r, seq); break;
+    case 4: hipLaunchKernelGGL((k_proll<MAXN, 4, ASC>), dim3(groups), dim3(256), 0, st, s, r, seq); break;
+    case 8: hipLaunchKernelGGL((k_proll<MAXN, 8, ASC>), dim3(groups), dim3(512), 0, st, s, r, seq); break;
     default: return -1;
   }
   return (int)hipGetLastError();
@@ -1685,17 +1840,15 @@ struct PipeL {
 };
 template <int MAXN, bool ASC, int FMT>
 struct RollL {
-  static int run(const DevState& s, const uint8_t* act, uint8_t* obs, int64_t obs_stride, float* rew,
-                 uint8_t* dn, uint8_t* pv, int T, int wpb, int groups, int nt, int wpe, hipStream_t st) {
-    return launch_roll_n<MAXN, ASC, FMT>(s, act, obs, obs_stride, rew, dn, pv, T, wpb, groups, nt, wpe, st);
+  static int run(const DevState& s, const RollIo& r, int wpb, int groups, int wpe, hipStream_t st) {
+    return launch_roll_n<MAXN, ASC, FMT>(s, r, wpb, groups, wpe, st);
   }
 };
 
 template <int MAXN, bool ASC, int FMT>
 struct PRollL {
-  static int run(const DevState& s, const uint8_t* act, uint8_t* obs, int64_t obs_stride, float* rew,
-                 uint8_t* dn, uint8_t* pv, int T, int wpb, int groups, int nt, uint32_t seq, hipStream_t st) {
-    return launch_proll_n<MAXN, ASC, FMT>(s, act, obs, obs_stride, rew, dn, pv, T, wpb, groups, nt, seq, st);
+  static int run(const DevState& s, const RollIo& r, int wpb, int groups, uint32_t seq, hipStream_t st) {
+    return launch_proll_n<MAXN, ASC, FMT>(s, r, wpb, groups, seq, st);
   }
 };
 
@@ -1760,6 +1913,7 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
                          int n_cu, uint32_t seq, void* stream) {
   if (s.n <= 0 || T <= 0) return 0;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  const RollIo r{act, obs, obs_stride, rew, dn, prev, T, lc.store_mode};
   if (lc.form == 1 && s.obs_fmt == 0) {
     // persistent: the chip's share of resident workgroups, never more than needed
     const int wpb = lc.waves_per_group;
@@ -1767,16 +1921,15 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
     const int need = (s.n + wpb - 1) / wpb;
     if (groups > need) groups = need;
     if (groups < 1) groups = 1;
-    return by_shape_f<PRollL, 0>(s, max_side, act, obs, obs_stride, rew, dn, prev, T, wpb, groups, lc.store_mode,
-                                 seq, st);
+    return by_shape_f<PRollL, 0>(s, max_side, r, wpb, groups, seq, st);
   }
-  const int wpb = s.obs_fmt != 0 ? kFmtWaves : lc.waves_per_group;
   const int wpe = lc.waves_per_env;
+  const int wpb = s.obs_fmt != 0 || wpe > 1 ? kFmtWaves : lc.waves_per_group;
   // wpe waves per env while they fit on the chip (16 waves per CU), else a stride
   int groups = (int)(((int64_t)s.n * wpe + wpb - 1) / wpb);
   const int cap = n_cu * (16 / wpb > 0 ? 16 / wpb : 1);
   if (groups > cap) groups = cap;
-  return by_shape<RollL>(s, max_side, act, obs, obs_stride, rew, dn, prev, T, wpb, groups, lc.store_mode, wpe, st);
+  return by_shape<RollL>(s, max_side, r, wpb, groups, wpe, st);
 }
 
 const char* kernel_error_string(int code) { return hipGetErrorString((hipError_t)code); }
