@@ -22,7 +22,10 @@ STORE_CEILING = os.path.join(PKG, "jx_store_ceiling")  # HBM store-pattern calib
 ARCH = os.environ.get("JX_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-DEVICE_SOURCES = ["jx_kernels.hip"]
+DEVICE_SOURCES = ["jx_kernels.hip", "jx_roll.hip", "jx_roll_narrow.hip"]
+# machine LICM hoists the step's constants out of the step loop into registers
+# that these kernels do not have
+EXTRA_FLAGS = {"jx_roll_narrow.hip": ["-mllvm", "-disable-machine-licm"]}
 HOST_SOURCES = ["jx_abi.cpp", "jx_host.cpp", "jx_layout.cpp", "jx_server.cpp"]
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", f"-I{INCLUDE}", f"-I{CSRC}"]
 DEVICE_FLAGS = ["-x", "hip", f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang",
@@ -38,7 +41,7 @@ def _obj_dir() -> str:
 
 def _compile(src: str, device: bool) -> str:
     obj = os.path.join(_obj_dir(), os.path.basename(src) + ".o")
-    cmd = [HIPCC] + COMMON + (DEVICE_FLAGS if device else HOST_FLAGS) + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + COMMON + (DEVICE_FLAGS if device else HOST_FLAGS) + EXTRA_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

@@ -263,7 +263,7 @@ static jx_status rollout_fused(jx_ctx* c, const DevState& S, int32_t T, const ui
   LaunchCfg lc = c->launch;
   if (lc.form == JX_FORM_PIPELINE) lc = LaunchCfg{0, 4, 1, lc.store_mode};
   int rc = launch_rollout_fused(S, actions, obs, obs_stride, reward, done, prev_action, T, lc, c->max_side,
-                                c->n_cu, seq, c->stream);
+                                c->n_cu, c->obs_off.back(), seq, c->stream);
   if (rc) return set_error(JX_EDEVICE, std::string("fused rollout launch: ") + kernel_error_string(rc));
   return JX_OK;
 }

@@ -1,0 +1,96 @@
+// jx_roll_narrow.hip -- fused rollout kernels built for few registers (gfx950):
+// several waves per env, and 4 one-wave envs per SIMD.  Compiled without machine
+// LICM (see build.py): hoisted, the constants of the double-precision sincos
+// alone hold 30 lane registers across the step loop, and a wave less fits on
+// each SIMD.
+#include "jx_roll.h"
+
+namespace jx {
+
+namespace {
+
+// Fused rollout with several waves per env (wpe 2 or 4), for batches that leave
+// the chip idle, where a step costs its latency: one wave steps and casts step
+// t (two waves do, half of the columns each, where four share an env whose rows
+// have more than 64 columns) while the others write step t - 1's frame.  The
+// records alternate between two LDS buffers, one workgroup barrier per step.
+// A workgroup's 4 waves hold 4 / wpe envs; all of them meet at every barrier.
+// 64 steps of 512 envs (25-side, 64 x 64): 219 us with one wave per env, 161 with
+// two and 169 with four (every wave stepping and casting for itself: 222, 223).
+template <int MAXN, bool ASC, int FMT>
+__global__ __launch_bounds__(256) void k_roll_split(DevState S, RollIo r, int wpe) {
+  __shared__ __align__(16) uint8_t smap[4][map_slice(MAXN)];
+  __shared__ __align__(16) uint32_t scol[2][2][2 * kMaxW];
+  __shared__ uint32_t sclr[kColorWords];
+  __shared__ uint32_t scvt[FMT % 3 ? 256 : 1];
+  stage_tables<FMT>(sclr, scvt);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+  const int slots = 4 / wpe, slot = w / wpe, part = w - slot * wpe;
+  const DevIo io = roll_step_io(r);
+  const int n = S.n;
+  for (int first = (int)blockIdx.x * slots; first < n; first += (int)gridDim.x * slots) {
+    // a slot past the last env runs that env once more and stores nothing
+    const bool live = first + slot < n;
+    int env, W, H;
+    int64_t obs_off;
+    {
+      const DevState& Q = kernarg_state();
+      env = __builtin_amdgcn_readfirstlane(Q.order[live ? first + slot : n - 1]);
+      const DevCfg& cf = Q.uniform ? Q.ucfg : Q.cfgs[Q.cfg_idx[env]];
+      W = (int)uniform_u((uint32_t)cf.obs_w);
+      H = (int)uniform_u((uint32_t)cf.obs_h);
+      obs_off = obs_off_of(Q, env);
+    }
+    const int casters = wpe == 4 && W > 64 ? 2 : 1;
+    if (part < casters) {
+      Carried<MAXN> c;
+      c.open(kernarg_state(), env, lane, smap[w] + guard_bytes(MAXN));
+      const bool store = live && lane == 0 && part == 0;
+      for (int t = 0; t < r.T; ++t) {
+        if ((t & 127) == 0) c.load_actions(n, r, t, lane);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        EnvOut o;
+        produce_env<MAXN, false, ASC>(c.in, io, c.action(t & 127), ln, smap[w] + guard_bytes(MAXN), sclr,
+                                      scol[slot][t & 1], o, part, casters);
+        c.take(n, r, o, t, store);
+        __syncthreads();
+      }
+      __syncthreads();  // the writers' last frame
+      if (store) c.close(kernarg_state());
+    } else {
+      uint8_t* at = r.obs + obs_off;
+      for (int t = 0; t < r.T; ++t) {
+        __syncthreads();  // step t's records are in buffer t & 1
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        if (live)
+          fill_frame<FMT, false>(scol[slot][t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, wpe - casters);
+        at += r.obs_stride;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+template <int MAXN, bool ASC, int FMT>
+struct SplitL {
+  static int run(const DevState& s, const RollIo& r, int groups, int wpe, hipStream_t st) {
+    hipLaunchKernelGGL((k_roll_split<MAXN, ASC, FMT>), dim3(groups), dim3(256), 0, st, s, r, wpe);
+    return (int)hipGetLastError();
+  }
+};
+
+}  // namespace
+
+int launch_roll_split(const DevState& s, int max_side, const RollIo& r, int groups, int wpe, hipStream_t st) {
+  return by_shape<SplitL>(s, max_side, r, groups, wpe, st);
+}
+
+int launch_roll_dense(const DevState& s, int max_side, const RollIo& r, int wpb, int groups, hipStream_t st) {
+  if (max_side <= 16) return launch_roll_n<16, false, 0, 4>(s, r, wpb, groups, st);
+  if (max_side <= 32) return launch_roll_n<32, false, 0, 4>(s, r, wpb, groups, st);
+  return launch_roll_n<64, false, 0, 4>(s, r, wpb, groups, st);
+}
+
+}  // namespace jx
