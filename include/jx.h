@@ -129,7 +129,9 @@ typedef struct {
                               waves_per_group; other forms: 1).  They divide the
                               casting and the writing of its frames, so small
                               batches and large frames use more of the chip;
-                              results do not change. */
+                              results do not change.  With 1 the library takes 2
+                              or 4 by itself where a batch leaves most of the
+                              chip idle. */
 } jx_launch;
 
 /* Per-column record of the last render (tests and tools).  hit = tile id of the

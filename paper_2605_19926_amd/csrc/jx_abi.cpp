@@ -41,6 +41,7 @@ struct jx_ctx {
   int max_side = 0, max_w = 0;
   int n_cu = 1;
   LaunchCfg launch{0, 1, 4, 0};
+  bool launch_chosen = false;  // by jx_set_launch or jx_autotune
   uint32_t seq = 0;  // persistent launches enqueued on this context's stream
   // static scratch of jx_rollout_noalloc on this device (looked up at create)
   uint32_t* scratch = nullptr;
@@ -56,13 +57,23 @@ struct jx_ctx {
       return set_error(JX_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// The mapping of a per-step launch.  A context whose mapping nobody has chosen
+// packs 4 waves into a workgroup: with one each, waves of envs that reset
+// together shared a SIMD more often (8192 key-door envs: 52.5 us a step against
+// 44.5; 4096 of 64 x 64: 15.6 and 14.7).
+static LaunchCfg step_launch(const jx_ctx* c) {
+  LaunchCfg l = c->launch;
+  if (!c->launch_chosen) l.waves_per_group = 4;
+  return l;
+}
+
 // Enqueues one step/render launch.  seq_override >= 0 fixes the persistent
 // queue sequence number (graph capture); otherwise the context's counter runs.
 static jx_status launch_or_fail(jx_ctx* c, const DevIo& io, hipStream_t st,
                                 const RolloutDesc* rd = nullptr, int t = 0,
                                 int64_t seq_override = -1) {
   const uint32_t seq = seq_override >= 0 ? (uint32_t)seq_override : c->seq;
-  int rc = launch_batch(c->S, io, rd, t, c->launch, c->max_side, c->n_cu, seq, st);
+  int rc = launch_batch(c->S, io, rd, t, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu, seq, st);
   if (rc == 0 && seq_override < 0 && c->launch.form == JX_FORM_PERSISTENT) c->seq += 1;
   if (rc != 0) return set_error(JX_EDEVICE, std::string("kernel launch: ") + kernel_error_string(rc));
   return JX_OK;
@@ -262,6 +273,10 @@ static jx_status rollout_fused(jx_ctx* c, const DevState& S, int32_t T, const ui
                                uint32_t seq) {
   LaunchCfg lc = c->launch;
   if (lc.form == JX_FORM_PIPELINE) lc = LaunchCfg{0, 4, 1, lc.store_mode};
+  // nobody's choice: 8 waves per workgroup fill the chip evenly where a stride
+  // runs (4096 envs of 64 x 64: 326 us for 32 steps, 342 with 4), 4 leave more
+  // room below that (2304: 267 and 212)
+  if (!c->launch_chosen) lc.waves_per_group = c->n > 12 * c->n_cu ? 8 : 4;
   int rc = launch_rollout_fused(S, actions, obs, obs_stride, reward, done, prev_action, T, lc, c->max_side,
                                 c->n_cu, c->obs_off.back(), seq, c->stream);
   if (rc) return set_error(JX_EDEVICE, std::string("fused rollout launch: ") + kernel_error_string(rc));
@@ -368,7 +383,8 @@ jx_status jx_rollout_noalloc(jx_ctx* c, int32_t T, const uint8_t* actions, uint8
   if (flags & JX_ROLLOUT_FUSED) return rollout_fused(c, S, T, actions, obs, obs_stride, reward, done, prev_action, 0);
   for (int t = 0; t < T; ++t) {
     const DevIo io = step_io(c, t, actions, obs, obs_stride, reward, done, prev_action);
-    const int rc = launch_batch(S, io, nullptr, 0, c->launch, c->max_side, c->n_cu, (uint32_t)t, c->stream);
+    const int rc = launch_batch(S, io, nullptr, 0, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu,
+                                (uint32_t)t, c->stream);
     if (rc != 0) return set_error(JX_EDEVICE, std::string("kernel launch: ") + kernel_error_string(rc));
   }
   return JX_OK;
@@ -493,6 +509,7 @@ jx_status jx_set_launch(jx_ctx* c, const jx_launch* l) {
   if (wpe != 1 && wpe != 2 && wpe != 4) return set_error(JX_EINVAL, "waves_per_env must be 1, 2 or 4");
   if (wpe > 1 && l->form != JX_FORM_PLAIN) return set_error(JX_EINVAL, "waves_per_env > 1 needs the plain form");
   if (wpe > w) return set_error(JX_EINVAL, "waves_per_env must not exceed waves_per_group");
+  c->launch_chosen = true;
   c->launch = LaunchCfg{l->form, w, std::max(1, l->groups_per_cu), l->store_mode, wpe};
   return JX_OK;
 }
@@ -580,6 +597,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   LaunchCfg hit{};
   if (cache_lookup(cache_path, key, &hit)) {
     c->launch = hit;
+    c->launch_chosen = true;
     if (chosen) jx_get_launch(c, chosen);
     return JX_OK;
   }
@@ -618,6 +636,8 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
     for (int g : {1, 2, 4})
       for (int s : {0, 1}) cands.push_back(LaunchCfg{2, p, g, s});
   const LaunchCfg keep = c->launch;
+  const bool keep_chosen = c->launch_chosen;
+  c->launch_chosen = true;
   std::vector<uint8_t> ref_obs(ob), ref_state(total), ref_io((size_t)iters * n * 5);
   std::vector<uint8_t> cur_obs(ob), cur_state(total), cur_io((size_t)iters * n * 5);
   float best_ms = 1e30f;
@@ -681,6 +701,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   hipFree(io_buf);
   if (result != JX_OK) {
     c->launch = keep;
+    c->launch_chosen = keep_chosen;
     return result;
   }
   c->launch = best;

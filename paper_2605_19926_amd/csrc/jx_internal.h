@@ -151,9 +151,11 @@ constexpr int kScratchWords = kQueueWords;
 static_assert(kScratchWords * 4 == 16384, "scratch size");
 
 // rd != nullptr: the I/O of step t is taken from the device descriptor rd.
+// max_w: the widest frame's columns; frames_bytes: of all envs' frames.
 // seq: launch sequence number (persistent form).
 int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t,
-                 const LaunchCfg& lc, int max_side, int n_cu, uint32_t seq, void* stream);
+                 const LaunchCfg& lc, int max_side, int max_w, int64_t frames_bytes, int n_cu, uint32_t seq,
+                 void* stream);
 int launch_clear_queues(uint32_t* queues, void* stream);
 // Device address of the static scratch array on `device`, looked up on the
 // first call for that device, which must be made with the device current.

@@ -9,50 +9,46 @@ namespace jx {
 
 namespace {
 
-// Fused rollout with several waves per env (wpe 2 or 4), for batches that leave
-// the chip idle, where a step costs its latency: one wave steps and casts step
-// t (two waves do, half of the columns each, where four share an env whose rows
-// have more than 64 columns) while the others write step t - 1's frame.  The
-// records alternate between two LDS buffers, one workgroup barrier per step.
-// A workgroup's 4 waves hold 4 / wpe envs; all of them meet at every barrier.
+// Fused rollout with several waves per env (WPE 2 or 4, a workgroup each): one
+// wave steps and casts step t (two waves do, half of the columns each, where four
+// share an env whose rows have more than 64 columns) while the others write step
+// t - 1's frame.  The records alternate between two LDS buffers, one workgroup
+// barrier per step.  Workgroups take envs by a static stride over the work order.
 // 64 steps of 512 envs (25-side, 64 x 64): 219 us with one wave per env, 161 with
 // two and 169 with four (every wave stepping and casting for itself: 222, 223).
-template <int MAXN, bool ASC, int FMT>
-__global__ __launch_bounds__(256) void k_roll_split(DevState S, RollIo r, int wpe) {
-  __shared__ __align__(16) uint8_t smap[4][map_slice(MAXN)];
-  __shared__ __align__(16) uint32_t scol[2][2][2 * kMaxW];
+template <int MAXN, bool ASC, int FMT, int WPE>
+__global__ __launch_bounds__(64 * WPE) void k_roll_split(DevState S, RollIo r) {
+  __shared__ __align__(16) uint8_t smap[WPE / 2][map_slice(MAXN)];
+  __shared__ __align__(16) uint32_t scol[2][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   __shared__ uint32_t scvt[FMT % 3 ? 256 : 1];
   stage_tables<FMT>(sclr, scvt);
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
-  const int slots = 4 / wpe, slot = w / wpe, part = w - slot * wpe;
+  const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
   const DevIo io = roll_step_io(r);
   const int n = S.n;
-  for (int first = (int)blockIdx.x * slots; first < n; first += (int)gridDim.x * slots) {
-    // a slot past the last env runs that env once more and stores nothing
-    const bool live = first + slot < n;
+  for (int item = (int)blockIdx.x; item < n; item += (int)gridDim.x) {
     int env, W, H;
     int64_t obs_off;
     {
       const DevState& Q = kernarg_state();
-      env = __builtin_amdgcn_readfirstlane(Q.order[live ? first + slot : n - 1]);
+      env = __builtin_amdgcn_readfirstlane(Q.order[item]);
       const DevCfg& cf = Q.uniform ? Q.ucfg : Q.cfgs[Q.cfg_idx[env]];
       W = (int)uniform_u((uint32_t)cf.obs_w);
       H = (int)uniform_u((uint32_t)cf.obs_h);
       obs_off = obs_off_of(Q, env);
     }
-    const int casters = wpe == 4 && W > 64 ? 2 : 1;
+    const int casters = WPE == 4 && W > 64 ? 2 : 1;
     if (part < casters) {
+      uint8_t* lmap = smap[WPE == 4 ? part : 0] + guard_bytes(MAXN);
       Carried<MAXN> c;
-      c.open(kernarg_state(), env, lane, smap[w] + guard_bytes(MAXN));
-      const bool store = live && lane == 0 && part == 0;
+      c.open(kernarg_state(), env, lane, lmap);
+      const bool store = lane == 0 && part == 0;
       for (int t = 0; t < r.T; ++t) {
         if ((t & 127) == 0) c.load_actions(n, r, t, lane);
         int ln = lane;
         asm volatile("" : "+v"(ln));
         EnvOut o;
-        produce_env<MAXN, false, ASC>(c.in, io, c.action(t & 127), ln, smap[w] + guard_bytes(MAXN), sclr,
-                                      scol[slot][t & 1], o, part, casters);
+        produce_env<MAXN, false, ASC>(c.in, io, c.action(t & 127), ln, lmap, sclr, scol[t & 1], o, part, casters);
         c.take(n, r, o, t, store);
         __syncthreads();
       }
@@ -64,8 +60,7 @@ __global__ __launch_bounds__(256) void k_roll_split(DevState S, RollIo r, int wp
         __syncthreads();  // step t's records are in buffer t & 1
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        if (live)
-          fill_frame<FMT, false>(scol[slot][t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, wpe - casters);
+        fill_frame<FMT, false>(scol[t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, WPE - casters);
         at += r.obs_stride;
       }
       __syncthreads();
@@ -76,7 +71,8 @@ __global__ __launch_bounds__(256) void k_roll_split(DevState S, RollIo r, int wp
 template <int MAXN, bool ASC, int FMT>
 struct SplitL {
   static int run(const DevState& s, const RollIo& r, int groups, int wpe, hipStream_t st) {
-    hipLaunchKernelGGL((k_roll_split<MAXN, ASC, FMT>), dim3(groups), dim3(256), 0, st, s, r, wpe);
+    if (wpe == 2) hipLaunchKernelGGL((k_roll_split<MAXN, ASC, FMT, 2>), dim3(groups), dim3(128), 0, st, s, r);
+    else hipLaunchKernelGGL((k_roll_split<MAXN, ASC, FMT, 4>), dim3(groups), dim3(256), 0, st, s, r);
     return (int)hipGetLastError();
   }
 };

@@ -74,3 +74,16 @@ def test_dense_rollouts_of_small_frames(n, wpb):
     cfg = W.env_cfg(obs_h=32, obs_w=32, episode_cap=5, **TREE)
     want = _run(cfg, n, 7, ONE, False)
     assert _same(_run(cfg, n, 7, dict(waves_per_group=wpb), True), want)
+
+
+@pytest.mark.parametrize("n,h,w,fmt", [(512, 64, 64, (0, 0)), (513, 64, 64, (0, 0)), (1536, 64, 64, (0, 0)),
+                                       (1537, 64, 64, (0, 0)), (768, 72, 80, (0, 0)), (1025, 84, 84, (0, 0)),
+                                       (769, 64, 64, (1, 1)), (30, 128, 128, (1, 2))])
+def test_mapping_left_to_the_library(n, h, w, fmt):
+    """Around the batches and frames from which an env gets more than one wave."""
+    cfg = W.env_cfg(obs_h=h, obs_w=w, episode_cap=6, obs_layout=fmt[0], obs_dtype=fmt[1], **TREE)
+    want = _run(cfg, n, 8, dict(form=2, waves_per_group=1, groups_per_cu=2) if fmt == (0, 0) else
+                dict(waves_per_group=4, waves_per_env=2), False)
+    for launch in (None, dict(waves_per_group=8)):
+        for fused in (False, True):
+            assert _same(_run(cfg, n, 8, launch, fused), want), (launch, fused)
