@@ -63,8 +63,10 @@ def _kernel_source_digest(text: str | None = None) -> str:
     import hashlib
     import re
     if text is None:
-        with open(os.path.join(ROOT, "paper_2605_19926_amd", "csrc", "jx_kernels.hip")) as f:
-            text = f.read()
+        text = ""
+        for name in ("jx_device.h", "jx_roll.h", "jx_roll.hip", "jx_roll_narrow.hip", "jx_kernels.hip"):
+            with open(os.path.join(ROOT, "paper_2605_19926_amd", "csrc", name)) as f:
+                text += f.read()
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", " ", text)
     return hashlib.sha256(" ".join(text.split()).encode()).hexdigest()[:16]
@@ -194,7 +196,7 @@ def cpu_baseline(wl: dict, tiny: dict, envs_per_worker: int = 64, cpu_seconds: f
 
 def batch_form(jx, torch, launches: list[dict], rollouts: int = 2) -> dict:
     """Mixed-shape batch (16384 envs: map side {8,16,32,64}, frames {32,64,128}
-    square, key-door on half) stepped by 128-step hipGraph rollouts; env-steps/s
+    square, key-door on half) in 128-step rollouts, fused or launch by launch; env-steps/s
     per launch mapping, the given ones and the one the library's autotuner picks
     (every candidate checked bit-identical to the default mapping)."""
     n, T = W.BATCH["n_envs"], W.BATCH["rollout"]
@@ -215,17 +217,17 @@ def batch_form(jx, torch, launches: list[dict], rollouts: int = 2) -> dict:
         launch = dict(launch)
         fused = launch.pop("fused", False)
         env.set_launch(**launch)
-        env.rollout(acts, obs, rew, done, T, obs_stride=ob, graph=not fused, fused=fused)  # warm
+        env.rollout(acts, obs, rew, done, T, obs_stride=ob, graph=False, fused=fused)  # warm
         torch.cuda.synchronize()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(rollouts):
-            env.rollout(acts, obs, rew, done, T, obs_stride=ob, graph=not fused, fused=fused)
+            env.rollout(acts, obs, rew, done, T, obs_stride=ob, graph=False, fused=fused)
         e1.record()
         torch.cuda.synchronize()
         sec = e0.elapsed_time(e1) / 1e3
         steps = rollouts * T
-        out["results"].append({"launch": launch, "rollout": "fused" if fused else "graph",
+        out["results"].append({"launch": launch, "rollout": "fused" if fused else "steps",
                                "autotuned": tuned,
                                "env_steps_per_s": n * steps / sec,
                                "ms_per_step": sec / steps * 1e3,
@@ -431,13 +433,9 @@ def main() -> int:
             else:
                 o = obs[slot * ob:] if slots > 1 else obs
                 env.rollout(acts[t:t + chunk], o, rew[slot * n:], done[slot * n:], chunk,
-                            obs_stride=ob if slots > 1 else 0, graph=args.form != "fused",
+                            obs_stride=ob if slots > 1 else 0, graph=args.form == "graph",
                             fused=args.form == "fused")
 
-    # capture every graph length the timed region will use before timing
-    if args.form not in ("eager", "fused"):
-        for T in sorted({c for _, _, c in plan(Wu, K)}):
-            env.rollout(acts[:T], obs, rew, done, T, obs_stride=ob if slots > 1 else 0, graph=True)
     run(0, Wu)
     torch.cuda.synchronize()
     ep_before = int(env.get_state()["episode"].astype(np.int64).sum())

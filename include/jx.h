@@ -216,18 +216,17 @@ jx_status jx_step(jx_ctx* ctx, const uint8_t* actions_dev, uint8_t* obs_dev, flo
                   uint8_t* done_dev, uint8_t* prev_action_dev);
 
 /* T consecutive steps (the paper's learner collects 128-step rollouts of
- * vmapped envs, Sec. 3.1, App. A.2 and the PPO hyperparameter table; graph
- * capture and the fused launch are this library's).  actions_dev[T][n]; step t
+ * vmapped envs, Sec. 3.1, App. A.2 and the PPO hyperparameter table; the
+ * fused launch is this library's).  actions_dev[T][n]; step t
  * writes its frames at
  * obs_dev + t*obs_stride (obs_stride >= jx_obs_bytes(), or 0 to write every
  * step into the same frame buffer), rewards at reward_dev + t*n, dones at
  * done_dev + t*n and, when prev_action_dev is not NULL, previous actions (as in
- * jx_step) at prev_action_dev + t*n.  flags & JX_ROLLOUT_GRAPH: the T
- * launches are captured once per (T, launch mapping) into a hipGraph and
- * replayed with one graph launch;
- * the buffers of each call reach the captured kernels through a descriptor in
- * the workspace, so a captured graph serves any buffers.  Without the flag the
- * T launches are enqueued one by one. */
+ * jx_step) at prev_action_dev + t*n.  flags & JX_ROLLOUT_GRAPH: the fastest way
+ * to run T steps whose actions are known, chosen by T and the batch: the fused
+ * launch below or, for a few steps of very many envs, T launches.  (It used to
+ * replay a captured graph of T launches, which the fused launch is faster than.)
+ * Without flags the T launches are enqueued one by one. */
 #define JX_ROLLOUT_GRAPH 1
 /* flags & JX_ROLLOUT_FUSED: one launch runs all T steps; each wave keeps its
  * env's state on chip between steps and writes it back after the last step.
@@ -257,7 +256,7 @@ jx_status jx_rollout(jx_ctx* ctx, int32_t T, const uint8_t* actions_dev, uint8_t
  * enqueues kernels on the context's stream: a kernel first clears the counters
  * the previous call left in the array, so a captured call replays correctly.
  * flags: 0 (T launches) or JX_ROLLOUT_FUSED (one launch); JX_ROLLOUT_GRAPH is
- * rejected with JX_EINVAL (instantiating a graph allocates).  Every call on a
+ * rejected with JX_EINVAL.  Every call on a
  * device shares that device's array: calls that overlap on one device (other
  * streams, threads or contexts) race and must be serialised by the caller.
  * JX_EDEVICE if the array could not be resolved when the context was created. */

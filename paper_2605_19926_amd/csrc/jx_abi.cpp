@@ -1,6 +1,6 @@
 // jx_abi.cpp -- host runtime behind include/jx.h: validation, workspace layout,
-// reset (host maze generation + device episode reset), step, hipGraph rollouts,
-// state import/export and the launch-mapping autotuner.
+// reset (host maze generation + device episode reset), step, rollouts, state
+// import/export and the launch-mapping autotuner.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -8,9 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <array>
 #include <fstream>
-#include <map>
 #include <numeric>
 #include <sstream>
 #include <string>
@@ -27,7 +25,6 @@ using namespace jx;
 struct jx_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
-  hipStream_t cap_stream = nullptr;
   uint8_t* ws = nullptr;
   size_t ws_bytes = 0;
   int n = -1;  // -1 until reset
@@ -46,8 +43,6 @@ struct jx_ctx {
   // static scratch of jx_rollout_noalloc on this device (looked up at create)
   uint32_t* scratch = nullptr;
   int scratch_err = 0;
-  // captured rollouts, keyed by (T, launch mapping)
-  std::map<std::array<int32_t, 6>, hipGraphExec_t> graphs;
 };
 
 #define HIPCHK(expr)                                                                   \
@@ -67,14 +62,11 @@ static LaunchCfg step_launch(const jx_ctx* c) {
   return l;
 }
 
-// Enqueues one step/render launch.  seq_override >= 0 fixes the persistent
-// queue sequence number (graph capture); otherwise the context's counter runs.
-static jx_status launch_or_fail(jx_ctx* c, const DevIo& io, hipStream_t st,
-                                const RolloutDesc* rd = nullptr, int t = 0,
-                                int64_t seq_override = -1) {
-  const uint32_t seq = seq_override >= 0 ? (uint32_t)seq_override : c->seq;
-  int rc = launch_batch(c->S, io, rd, t, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu, seq, st);
-  if (rc == 0 && seq_override < 0 && c->launch.form == JX_FORM_PERSISTENT) c->seq += 1;
+// Enqueues one step/render launch on the context's stream.
+static jx_status launch_or_fail(jx_ctx* c, const DevIo& io) {
+  int rc = launch_batch(c->S, io, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu, c->seq,
+                        c->stream);
+  if (rc == 0 && c->launch.form == JX_FORM_PERSISTENT) c->seq += 1;
   if (rc != 0) return set_error(JX_EDEVICE, std::string("kernel launch: ") + kernel_error_string(rc));
   return JX_OK;
 }
@@ -125,19 +117,12 @@ jx_status jx_create(jx_ctx** out, int32_t device, void* hip_stream, void* worksp
   // the device is current: resolve this device's copy of the static scratch
   // array once, here, so the entry point that allocates nothing needs no set-up
   c->scratch_err = scratch_device_address(device, &c->scratch);
-  if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) {
-    delete c;
-    return set_error(JX_EDEVICE, "stream creation failed");
-  }
   *out = c;
   return JX_OK;
 }
 
 void jx_destroy(jx_ctx* c) {
   if (!c) return;
-  hipSetDevice(c->device);
-  for (auto& kv : c->graphs) hipGraphExecDestroy(kv.second);
-  if (c->cap_stream) hipStreamDestroy(c->cap_stream);
   delete c;
 }
 
@@ -167,8 +152,6 @@ jx_status jx_reset(jx_ctx* c, int32_t n_envs, const uint64_t* seeds, const jx_en
   if ((size_t)L.total > c->ws_bytes)
     return set_error(JX_ENOMEM, "workspace too small: need " + std::to_string(L.total) + " bytes");
   HIPCHK(hipSetDevice(c->device));
-  for (auto& kv : c->graphs) hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
   HIPCHK(hipMemcpyAsync(c->ws, img.data(), (size_t)L.total, hipMemcpyHostToDevice, c->stream));
   c->L = L;
   c->n = n_envs;
@@ -201,7 +184,7 @@ jx_status jx_reset(jx_ctx* c, int32_t n_envs, const uint64_t* seeds, const jx_en
   if (n_envs > 0) {
     LaunchCfg keep = c->launch;
     c->launch = LaunchCfg{0, 1, 1, 0};
-    jx_status r = launch_or_fail(c, io, c->stream);
+    jx_status r = launch_or_fail(c, io);
     c->launch = keep;
     if (r != JX_OK) return r;
   }
@@ -241,7 +224,7 @@ jx_status jx_step(jx_ctx* c, const uint8_t* actions, uint8_t* obs, float* reward
   io.prev = prev_action;
   io.mode = MODE_STEP;
   io.store_mode = c->launch.store_mode;
-  return launch_or_fail(c, io, c->stream);
+  return launch_or_fail(c, io);
 }
 
 // Arguments of a T-step rollout.  JX_OK with *nothing = true when there is no
@@ -304,56 +287,25 @@ jx_status jx_rollout(jx_ctx* c, int32_t T, const uint8_t* actions, uint8_t* obs,
   jx_status st = check_rollout(c, T, actions, obs, obs_stride, reward, done, &nothing);
   if (st || nothing) return st;
   HIPCHK(hipSetDevice(c->device));
-  if (flags & JX_ROLLOUT_FUSED) {
+  // One launch for all steps.  JX_ROLLOUT_GRAPH asks for one launch in the caller's
+  // time and takes it too: it carries each env through its steps on chip, where a
+  // graph of per-step launches pays about 2 us between them and the load of every
+  // env's state each time (64 steps of 1024 envs of 64 x 64: 610 us as a graph, 205
+  // fused; 32 steps of 16384: 1327 and 1301).  A single step, and up to 3 of very
+  // many envs with larger byte frames, go launch by launch, where more waves fit on
+  // the chip and the host stays ahead (16384 envs of 64 x 64: 1 step 37 us, 54
+  // fused; 2 steps 85 and 104; 4 steps 166 and 172).
+  const bool few = T == 1 || (T < 4 && c->n > 32 * c->n_cu && c->S.obs_fmt == 0 &&
+                              c->obs_off.back() >= (int64_t)c->n * 8192);
+  if ((flags & JX_ROLLOUT_FUSED) || ((flags & JX_ROLLOUT_GRAPH) && !few)) {
     st = rollout_fused(c, c->S, T, actions, obs, obs_stride, reward, done, prev_action, c->seq);
     if (st == JX_OK && c->launch.form == JX_FORM_PERSISTENT) c->seq += 1;
     return st;
   }
-  if (!(flags & JX_ROLLOUT_GRAPH)) {
-    for (int t = 0; t < T; ++t) {
-      st = launch_or_fail(c, step_io(c, t, actions, obs, obs_stride, reward, done, prev_action), c->stream);
-      if (st) return st;
-    }
-    return JX_OK;
+  for (int t = 0; t < T; ++t) {
+    st = launch_or_fail(c, step_io(c, t, actions, obs, obs_stride, reward, done, prev_action));
+    if (st) return st;
   }
-  // The captured kernels read their buffers from the workspace descriptor,
-  // so one graph per (T, mapping) serves every call.
-  RolloutDesc d{actions, obs, reward, done, prev_action, obs_stride, c->n, c->launch.store_mode};
-  int rc = launch_set_desc(c->S.rdesc, d, c->stream);
-  if (rc) return set_error(JX_EDEVICE, std::string("descriptor update: ") + kernel_error_string(rc));
-  const std::array<int32_t, 6> key = {T, c->launch.form, c->launch.waves_per_group, c->launch.waves_per_env,
-                                      c->launch.groups_per_cu, c->launch.store_mode};
-  auto it = c->graphs.find(key);
-  if (it == c->graphs.end()) {
-    hipGraph_t g = nullptr;
-    HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-    jx_status lst = JX_OK;
-    DevIo io{};
-    io.mode = MODE_STEP;
-    // a kernel (not a memset node) clears the queue counters at the head
-    if (c->launch.form == JX_FORM_PERSISTENT && launch_clear_queues(c->S.queues, c->cap_stream) != 0)
-      lst = set_error(JX_EDEVICE, "queue clear launch failed");
-    for (int t = 0; t < T && lst == JX_OK; ++t)
-      lst = launch_or_fail(c, io, c->cap_stream, c->S.rdesc, t, t);
-    hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
-    if (lst != JX_OK) {
-      if (g) hipGraphDestroy(g);
-      return lst;
-    }
-    if (e != hipSuccess) return set_error(JX_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-    hipGraphExec_t ge = nullptr;
-    e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    hipGraphDestroy(g);
-    if (e != hipSuccess) return set_error(JX_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
-    if (c->graphs.size() >= 8) {
-      hipGraphExecDestroy(c->graphs.begin()->second);
-      c->graphs.erase(c->graphs.begin());
-    }
-    it = c->graphs.emplace(key, ge).first;
-  }
-  HIPCHK(hipGraphLaunch(it->second, c->stream));
-  // the replay's last launch cleared counter set T % 4: continue from there
-  if (c->launch.form == JX_FORM_PERSISTENT) c->seq = (uint32_t)T;
   return JX_OK;
 }
 
@@ -364,7 +316,7 @@ jx_status jx_rollout_noalloc(jx_ctx* c, int32_t T, const uint8_t* actions, uint8
   if (st) return st;
   if (flags & ~JX_ROLLOUT_FUSED)
     return set_error(JX_EINVAL, flags & JX_ROLLOUT_GRAPH
-                                    ? "JX_ROLLOUT_GRAPH is not accepted: instantiating a graph allocates (use jx_rollout)"
+                                    ? "JX_ROLLOUT_GRAPH is not accepted by the entry point that allocates nothing (use jx_rollout)"
                                     : "unknown rollout flags");
   if (nothing) return JX_OK;
   if (!c->scratch)
@@ -383,7 +335,7 @@ jx_status jx_rollout_noalloc(jx_ctx* c, int32_t T, const uint8_t* actions, uint8
   if (flags & JX_ROLLOUT_FUSED) return rollout_fused(c, S, T, actions, obs, obs_stride, reward, done, prev_action, 0);
   for (int t = 0; t < T; ++t) {
     const DevIo io = step_io(c, t, actions, obs, obs_stride, reward, done, prev_action);
-    const int rc = launch_batch(S, io, nullptr, 0, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu,
+    const int rc = launch_batch(S, io, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu,
                                 (uint32_t)t, c->stream);
     if (rc != 0) return set_error(JX_EDEVICE, std::string("kernel launch: ") + kernel_error_string(rc));
   }
@@ -403,12 +355,12 @@ jx_status jx_render(jx_ctx* c, uint8_t* obs, jx_col_debug* dbg) {
   io.dbg_stride = c->max_w;
   io.mode = MODE_RENDER;
   io.store_mode = c->launch.store_mode;
-  return launch_or_fail(c, io, c->stream);
+  return launch_or_fail(c, io);
 }
 
 size_t jx_state_bytes(const jx_ctx* c) {
   if (!c || c->n < 0) return 0;
-  return (size_t)c->L.rdesc;
+  return (size_t)c->L.spare;
 }
 
 jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_fields) {
@@ -443,7 +395,7 @@ jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_
              {"obs_offset", L.obs_off, 8, (int64_t)n + 1},
              {"order", L.order, 4, n},
              {"cfgs", L.cfgs, (int)sizeof(DevCfg), (int64_t)c->cfgs.size()},
-             {"maps", L.maps, 1, L.rdesc - L.maps}};
+             {"maps", L.maps, 1, L.spare - L.maps}};
   const int total = (int)(sizeof(all) / sizeof(all[0]));
   if (n_fields) *n_fields = total;
   if (!f) return JX_OK;
@@ -461,9 +413,9 @@ jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_
 jx_status jx_get_state(const jx_ctx* c, void* host, size_t bytes) {
   jx_status st = check_ready(c);
   if (st) return st;
-  if (!host || bytes < (size_t)c->L.rdesc) return set_error(JX_EINVAL, "host buffer too small");
+  if (!host || bytes < (size_t)c->L.spare) return set_error(JX_EINVAL, "host buffer too small");
   HIPCHK(hipSetDevice(c->device));
-  HIPCHK(hipMemcpyAsync(host, c->ws, (size_t)c->L.rdesc, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipMemcpyAsync(host, c->ws, (size_t)c->L.spare, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return JX_OK;
 }
@@ -471,11 +423,11 @@ jx_status jx_get_state(const jx_ctx* c, void* host, size_t bytes) {
 jx_status jx_set_state(jx_ctx* c, const void* host, size_t bytes) {
   jx_status st = check_ready(c);
   if (st) return st;
-  if (!host || bytes < (size_t)c->L.rdesc) return set_error(JX_EINVAL, "state image too small");
+  if (!host || bytes < (size_t)c->L.spare) return set_error(JX_EINVAL, "state image too small");
   const uint8_t* b = (const uint8_t*)host;
   WsHeader h;
   std::memcpy(&h, b + c->L.hdr, sizeof(h));
-  if (h.magic != kStateMagic || h.n_envs != c->n || h.state_bytes != c->L.rdesc ||
+  if (h.magic != kStateMagic || h.n_envs != c->n || h.state_bytes != c->L.spare ||
       h.n_cfgs != (int32_t)c->cfgs.size())
     return set_error(JX_EINVAL, "state image does not match this context");
   if (std::memcmp(b + c->L.cfgs, c->dev_cfgs.data(), sizeof(DevCfg) * c->dev_cfgs.size()) != 0 ||
@@ -485,7 +437,7 @@ jx_status jx_set_state(jx_ctx* c, const void* host, size_t bytes) {
   // every index the kernels dereference must be in range
   st = check_state_image(b, c->L, c->n, c->cfgs, c->cfg_idx);
   if (st) return st;
-  std::vector<uint8_t> img(b, b + c->L.rdesc);
+  std::vector<uint8_t> img(b, b + c->L.spare);
   WsHeader* hh = (WsHeader*)(img.data() + c->L.hdr);
   hh->queue = 0;
   hh->exited = 0;
@@ -601,7 +553,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
     if (chosen) jx_get_launch(c, chosen);
     return JX_OK;
   }
-  const size_t total = (size_t)c->L.rdesc;  // the state image
+  const size_t total = (size_t)c->L.spare;  // the state image
   const int64_t ob = c->obs_off.back();
   const int n = c->n;
   uint8_t* snap = nullptr;
@@ -660,7 +612,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
         io.done = dn + (int64_t)t * n;
         io.mode = MODE_STEP;
         io.store_mode = c->launch.store_mode;
-        result = launch_or_fail(c, io, c->stream);
+        result = launch_or_fail(c, io);
       }
       if (result != JX_OK) break;
       float ms = 0.f;

@@ -56,19 +56,9 @@ struct WsHeader {
 };
 static_assert(sizeof(WsHeader) == 256, "header size");
 
-// Device-resident I/O of a captured rollout: step t uses act + t*n,
-// obs + t*obs_stride, rew + t*n, done + t*n.  Written by a one-thread kernel
-// before each graph replay, so one captured graph serves any buffers.
-struct RolloutDesc {
-  const uint8_t* act;
-  uint8_t* obs;
-  float* rew;
-  uint8_t* done;
-  uint8_t* prev;  // nullable: previous actions, prev + t*n
-  int64_t obs_stride;
-  int32_t n;
-  int32_t store_mode;
-};
+// Bytes between the state image and the queues, kept so that the workspace of a
+// batch keeps its size.
+constexpr int64_t kSpareBytes = 56;
 
 // Device view of one batch of environments (pointers into one workspace).
 struct DevState {
@@ -92,7 +82,6 @@ struct DevState {
   const uint32_t* map_off;
   const int64_t* obs_off;  // [n+1]
   const int32_t* order;    // persistent work order (costliest first)
-  RolloutDesc* rdesc;      // rollout I/O descriptor
   uint32_t* queues;        // persistent form: [4 slots][32 queues][32] counters
   const DevCfg* cfgs;
   const uint8_t* maps;
@@ -131,7 +120,7 @@ struct ServeItem {
 // Workspace layout: byte offsets of every array.
 struct Layout {
   int64_t hdr, x, y, th, t, ep, goal, door, key, decor, akey, doors, flags, events, ndecor, invalid, seed,
-      cfg_idx, map_off, obs_off, order, rdesc, queues, cfgs, maps, total;
+      cfg_idx, map_off, obs_off, order, spare, queues, cfgs, maps, total;
 };
 
 // Launch entry points implemented in jx_kernels.hip.
@@ -150,11 +139,9 @@ constexpr int kQueueWords = kQueues * kQueueSlots * kQueueStride;
 constexpr int kScratchWords = kQueueWords;
 static_assert(kScratchWords * 4 == 16384, "scratch size");
 
-// rd != nullptr: the I/O of step t is taken from the device descriptor rd.
 // max_w: the widest frame's columns; frames_bytes: of all envs' frames.
 // seq: launch sequence number (persistent form).
-int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t,
-                 const LaunchCfg& lc, int max_side, int max_w, int64_t frames_bytes, int n_cu, uint32_t seq,
+int launch_batch(const DevState& s, const DevIo& io, const LaunchCfg& lc, int max_side, int max_w, int64_t frames_bytes, int n_cu, uint32_t seq,
                  void* stream);
 int launch_clear_queues(uint32_t* queues, void* stream);
 // Device address of the static scratch array on `device`, looked up on the
@@ -168,7 +155,6 @@ int scratch_device_address(int device, uint32_t** out);
 int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, int64_t obs_stride,
                          float* rew, uint8_t* dn, uint8_t* prev, int T, const LaunchCfg& lc, int max_side, int n_cu,
                          int64_t frames_bytes, uint32_t seq, void* stream);
-int launch_set_desc(RolloutDesc* rd_dev, const RolloutDesc& value, void* stream);
 int launch_serve(const DevState* states_dev, const DevIo* ios_dev, const ServeItem* items_dev,
                  int n_items, uint32_t* queues_dev, uint32_t seq, int waves_per_group,
                  int n_groups, void* stream);

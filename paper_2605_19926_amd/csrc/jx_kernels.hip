@@ -8,24 +8,9 @@ namespace jx {
 
 namespace {
 
-// I/O of this launch: given by value, or (graph replays) from the descriptor.
-__device__ __forceinline__ DevIo io_of(const DevIo& io, const RolloutDesc* rd, int t) {
-  if (!rd) return io;
-  DevIo r = io;
-  const int64_t n = rd->n;
-  r.act = rd->act + (int64_t)t * n;
-  r.obs = rd->obs + (int64_t)t * rd->obs_stride;
-  r.rew = rd->rew + (int64_t)t * n;
-  r.done = rd->done + (int64_t)t * n;
-  r.prev = rd->prev ? rd->prev + (int64_t)t * n : nullptr;
-  r.store_mode = rd->store_mode;
-  return r;
-}
-
 // wpe waves per env (1, 2 or 4): consecutive waves of a workgroup share an env.
 template <int MAXN, int WPB, bool ASC, int FMT>
-__global__ __launch_bounds__(64 * WPB) void k_plain(DevState S, DevIo io0, const RolloutDesc* rd,
-                                                    int t, int wpe) {
+__global__ __launch_bounds__(64 * WPB) void k_plain(DevState S, DevIo io, int wpe) {
   __shared__ __align__(16) uint8_t smap[WPB][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
@@ -35,20 +20,17 @@ __global__ __launch_bounds__(64 * WPB) void k_plain(DevState S, DevIo io0, const
   const int gw = __builtin_amdgcn_readfirstlane((int)blockIdx.x * WPB + w);
   const int env = gw / wpe, part = gw - env * wpe;
   if (wpe == 1 && env >= S.n) return;
-  const DevIo io = io_of(io0, rd, t);
   process_env<MAXN, ASC, FMT>(S, io, env, lane, smap[w] + guard_bytes(MAXN), sclr, scvt, scol[w - part], part, wpe,
                               env < S.n);
 }
 
 template <int WPB, bool ASC>
-__global__ __launch_bounds__(64 * WPB) void k_persist(DevState S, DevIo io0, const RolloutDesc* rd,
-                                                      int t, uint32_t seq) {
+__global__ __launch_bounds__(64 * WPB) void k_persist(DevState S, DevIo io, uint32_t seq) {
   __shared__ __align__(16) uint8_t smap[WPB][map_slice(kMaxSide)];
   __shared__ __align__(16) uint32_t scol[WPB][2 * kMaxW];
   __shared__ uint32_t sclr[kColorWords];
   stage_colors(sclr);
   const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  const DevIo io = io_of(io0, rd, t);
   const QueueView v = queue_view<WPB>(S.queues, seq, S.n, w, lane);
   queue_drain(v, lane, [&](int pos) {
     const int env = __builtin_amdgcn_readfirstlane(S.order[pos]);
@@ -86,8 +68,7 @@ __global__ __launch_bounds__(64 * WPB) void k_serve(const DevState* states, cons
 // never stall a load.  Pairs walk the work order (costliest first) with a
 // static stride of all pairs in the grid.
 template <int MAXN, int P, bool ASC>
-__global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const RolloutDesc* rd,
-                                                  int t) {
+__global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io) {
   __shared__ __align__(16) uint8_t smap[P][map_slice(MAXN)];
   __shared__ __align__(16) uint32_t scol[P][2][2 * kMaxW];
   __shared__ EnvOut sout[P][2];
@@ -96,7 +77,6 @@ __global__ __launch_bounds__(128 * P) void k_pipe(DevState S, DevIo io0, const R
   const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
   const int pair = w >> 1;
   const bool writer = (w & 1) != 0;
-  const DevIo io = io_of(io0, rd, t);
   const int pairs = (int)gridDim.x * P;
   const int gp = (int)blockIdx.x * P + pair;
   const int lead = (int)blockIdx.x * P;  // the workgroup's pair with the most items
@@ -133,25 +113,21 @@ __global__ void k_clear_queues(uint32_t* q) {
   for (int i = (int)threadIdx.x; i < kQueueWords; i += (int)blockDim.x) q[i] = 0u;
 }
 
-__global__ void k_set_desc(RolloutDesc* rd, RolloutDesc v) {
-  if (threadIdx.x == 0) *rd = v;
-}
-
 template <int MAXN, bool ASC, int FMT>
-int launch_plain_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t, int wpb, int wpe,
+int launch_plain_n(const DevState& s, const DevIo& io, int wpb, int wpe,
                    hipStream_t st) {
   if constexpr (FMT != 0) {
     const int grid = (int)(((int64_t)s.n * wpe + kFmtWaves - 1) / kFmtWaves);
     hipLaunchKernelGGL((k_plain<MAXN, kFmtWaves, ASC, FMT>), dim3(grid), dim3(64 * kFmtWaves), 0, st, s, io,
-                       rd, t, wpe);
+                       wpe);
     return (int)hipGetLastError();
   } else {
     const int grid = (int)(((int64_t)s.n * wpe + wpb - 1) / wpb);
     switch (wpb) {
-      case 1: hipLaunchKernelGGL((k_plain<MAXN, 1, ASC, 0>), dim3(grid), dim3(64), 0, st, s, io, rd, t, wpe); break;
-      case 2: hipLaunchKernelGGL((k_plain<MAXN, 2, ASC, 0>), dim3(grid), dim3(128), 0, st, s, io, rd, t, wpe); break;
-      case 4: hipLaunchKernelGGL((k_plain<MAXN, 4, ASC, 0>), dim3(grid), dim3(256), 0, st, s, io, rd, t, wpe); break;
-      case 8: hipLaunchKernelGGL((k_plain<MAXN, 8, ASC, 0>), dim3(grid), dim3(512), 0, st, s, io, rd, t, wpe); break;
+      case 1: hipLaunchKernelGGL((k_plain<MAXN, 1, ASC, 0>), dim3(grid), dim3(64), 0, st, s, io, wpe); break;
+      case 2: hipLaunchKernelGGL((k_plain<MAXN, 2, ASC, 0>), dim3(grid), dim3(128), 0, st, s, io, wpe); break;
+      case 4: hipLaunchKernelGGL((k_plain<MAXN, 4, ASC, 0>), dim3(grid), dim3(256), 0, st, s, io, wpe); break;
+      case 8: hipLaunchKernelGGL((k_plain<MAXN, 8, ASC, 0>), dim3(grid), dim3(512), 0, st, s, io, wpe); break;
       default: return -1;
     }
     return (int)hipGetLastError();
@@ -161,30 +137,30 @@ int launch_plain_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, in
 }  // namespace
 
 // Reset, render-only and debug launches always take the plain kernel.
-inline bool mode_needs_plain(const DevIo& io, const RolloutDesc* rd) {
-  return !rd && (io.mode != MODE_STEP || io.dbg != nullptr || io.obs == nullptr);
+inline bool mode_needs_plain(const DevIo& io) {
+  return io.mode != MODE_STEP || io.dbg != nullptr || io.obs == nullptr;
 }
 
 template <int MAXN, bool ASC, int FMT>
-int launch_pipe_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t, int p, int groups,
+int launch_pipe_n(const DevState& s, const DevIo& io, int p, int groups,
                   hipStream_t st) {
   switch (p) {
-    case 1: hipLaunchKernelGGL((k_pipe<MAXN, 1, ASC>), dim3(groups), dim3(128), 0, st, s, io, rd, t); break;
-    case 2: hipLaunchKernelGGL((k_pipe<MAXN, 2, ASC>), dim3(groups), dim3(256), 0, st, s, io, rd, t); break;
-    case 4: hipLaunchKernelGGL((k_pipe<MAXN, 4, ASC>), dim3(groups), dim3(512), 0, st, s, io, rd, t); break;
+    case 1: hipLaunchKernelGGL((k_pipe<MAXN, 1, ASC>), dim3(groups), dim3(128), 0, st, s, io); break;
+    case 2: hipLaunchKernelGGL((k_pipe<MAXN, 2, ASC>), dim3(groups), dim3(256), 0, st, s, io); break;
+    case 4: hipLaunchKernelGGL((k_pipe<MAXN, 4, ASC>), dim3(groups), dim3(512), 0, st, s, io); break;
     default: return -1;
   }
   return (int)hipGetLastError();
 }
 
 template <bool ASC>
-int launch_persist_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t, int wpb,
+int launch_persist_n(const DevState& s, const DevIo& io, int wpb,
                      int groups, uint32_t seq, hipStream_t st) {
   switch (wpb) {
-    case 1: hipLaunchKernelGGL((k_persist<1, ASC>), dim3(groups), dim3(64), 0, st, s, io, rd, t, seq); break;
-    case 2: hipLaunchKernelGGL((k_persist<2, ASC>), dim3(groups), dim3(128), 0, st, s, io, rd, t, seq); break;
-    case 4: hipLaunchKernelGGL((k_persist<4, ASC>), dim3(groups), dim3(256), 0, st, s, io, rd, t, seq); break;
-    case 8: hipLaunchKernelGGL((k_persist<8, ASC>), dim3(groups), dim3(512), 0, st, s, io, rd, t, seq); break;
+    case 1: hipLaunchKernelGGL((k_persist<1, ASC>), dim3(groups), dim3(64), 0, st, s, io, seq); break;
+    case 2: hipLaunchKernelGGL((k_persist<2, ASC>), dim3(groups), dim3(128), 0, st, s, io, seq); break;
+    case 4: hipLaunchKernelGGL((k_persist<4, ASC>), dim3(groups), dim3(256), 0, st, s, io, seq); break;
+    case 8: hipLaunchKernelGGL((k_persist<8, ASC>), dim3(groups), dim3(512), 0, st, s, io, seq); break;
     default: return -1;
   }
   return (int)hipGetLastError();
@@ -192,31 +168,25 @@ int launch_persist_n(const DevState& s, const DevIo& io, const RolloutDesc* rd, 
 
 template <int MAXN, bool ASC, int FMT>
 struct PlainL {
-  static int run(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t, int wpb, int wpe,
+  static int run(const DevState& s, const DevIo& io, int wpb, int wpe,
                  hipStream_t st) {
-    return launch_plain_n<MAXN, ASC, FMT>(s, io, rd, t, wpb, wpe, st);
+    return launch_plain_n<MAXN, ASC, FMT>(s, io, wpb, wpe, st);
   }
 };
 template <int MAXN, bool ASC, int FMT>
 struct PipeL {
-  static int run(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t, int p, int groups,
+  static int run(const DevState& s, const DevIo& io, int p, int groups,
                  hipStream_t st) {
-    return launch_pipe_n<MAXN, ASC, FMT>(s, io, rd, t, p, groups, st);
+    return launch_pipe_n<MAXN, ASC, FMT>(s, io, p, groups, st);
   }
 };
-int launch_set_desc(RolloutDesc* rd_dev, const RolloutDesc& value, void* stream) {
-  hipLaunchKernelGGL(k_set_desc, dim3(1), dim3(64), 0, reinterpret_cast<hipStream_t>(stream), rd_dev,
-                     value);
-  return (int)hipGetLastError();
-}
-
 int launch_clear_queues(uint32_t* queues, void* stream) {
   hipLaunchKernelGGL(k_clear_queues, dim3(1), dim3(256), 0, reinterpret_cast<hipStream_t>(stream),
                      queues);
   return (int)hipGetLastError();
 }
 
-int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int t,
+int launch_batch(const DevState& s, const DevIo& io,
                  const LaunchCfg& lc, int max_side, int max_w, int64_t frames_bytes, int n_cu, uint32_t seq,
                  void* stream) {
   if (s.n <= 0) return 0;
@@ -225,7 +195,7 @@ int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int 
   // training-buffer formats: plain form only.  Several waves per env only for
   // steps and renders that write frames (resets and debug records take one).
   if (lc.form == 0 || s.obs_fmt != 0) {
-    const bool frames = rd != nullptr || (io.mode != MODE_RESET && io.obs != nullptr && io.dbg == nullptr);
+    const bool frames = io.mode != MODE_RESET && io.obs != nullptr && io.dbg == nullptr;
     int wpe = frames ? lc.waves_per_env : 1, wpg = wpb;
     // Where the caller asks for one wave per env and the batch leaves most of the
     // chip idle, frames of 16 KB and more take four: one wave would write each
@@ -237,7 +207,7 @@ int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int 
       wpe = 4;
       if (wpg < 4) wpg = 4;
     }
-    return by_shape<PlainL>(s, max_side, io, rd, t, wpg, wpe, st);
+    return by_shape<PlainL>(s, max_side, io, wpg, wpe, st);
   }
   if (lc.form == 2) {
     // waves_per_group counts wave pairs (1, 2 or 4) in the pipelined form
@@ -246,15 +216,15 @@ int launch_batch(const DevState& s, const DevIo& io, const RolloutDesc* rd, int 
     const int need = (s.n + p - 1) / p;
     if (groups > need) groups = need;
     if (groups < 1) groups = 1;
-    if (mode_needs_plain(io, rd)) return by_shape<PlainL>(s, 64, io, rd, t, 1, 1, st);
-    return by_shape_f<PipeL, 0>(s, max_side, io, rd, t, p, groups, st);
+    if (mode_needs_plain(io)) return by_shape<PlainL>(s, 64, io, 1, 1, st);
+    return by_shape_f<PipeL, 0>(s, max_side, io, p, groups, st);
   }
   int groups = n_cu * lc.groups_per_cu;
   const int need = (s.n + wpb - 1) / wpb;
   if (groups > need) groups = need;
   if (groups < 1) groups = 1;
-  return s.any_ascii ? launch_persist_n<true>(s, io, rd, t, wpb, groups, seq, st)
-                     : launch_persist_n<false>(s, io, rd, t, wpb, groups, seq, st);
+  return s.any_ascii ? launch_persist_n<true>(s, io, wpb, groups, seq, st)
+                     : launch_persist_n<false>(s, io, wpb, groups, seq, st);
 }
 
 int launch_serve(const DevState* states_dev, const DevIo* ios_dev, const ServeItem* items_dev,

@@ -302,7 +302,7 @@ jx_status activate(jx_server* s, Client* c) {
     return set_error(JX_EDEVICE, "client upload failed");
   DevIo io{};
   io.mode = MODE_RESET;
-  int rc = launch_batch(c->S, io, nullptr, 0, LaunchCfg{0, 1, 1, 0}, c->cfg.side, c->cfg.obs_w, c->obs_bytes, s->n_cu,
+  int rc = launch_batch(c->S, io, LaunchCfg{0, 1, 1, 0}, c->cfg.side, c->cfg.obs_w, c->obs_bytes, s->n_cu,
                         0, s->admin);
   if (rc) return set_error(JX_EDEVICE, std::string("client reset: ") + kernel_error_string(rc));
   if (hipStreamSynchronize(s->admin) != hipSuccess) return set_error(JX_EDEVICE, "client reset sync failed");
@@ -470,7 +470,7 @@ void issue(jx_server* s, std::unique_lock<std::mutex>& lk, int k, const std::vec
       // the per-request kernel takes its state and I/O by value: copy the actions only
       ok = hipMemcpyAsync(d + P.acts, h + P.acts, (size_t)(P.results - P.acts), hipMemcpyHostToDevice, st) ==
            hipSuccess;
-      ok = ok && launch_batch(states[0], ios[0], nullptr, 0, LaunchCfg{0, 1, 1, 0}, side, first_w, first_obs, s->n_cu, 0, st) == 0;
+      ok = ok && launch_batch(states[0], ios[0], LaunchCfg{0, 1, 1, 0}, side, first_w, first_obs, s->n_cu, 0, st) == 0;
     } else {
       std::memcpy(h + P.states, states.data(), sizeof(DevState) * states.size());
       ok = hipMemcpyAsync(d, h, (size_t)P.results, hipMemcpyHostToDevice, st) == hipSuccess;

@@ -87,3 +87,25 @@ def test_mapping_left_to_the_library(n, h, w, fmt):
     for launch in (None, dict(waves_per_group=8)):
         for fused in (False, True):
             assert _same(_run(cfg, n, 8, launch, fused), want), (launch, fused)
+
+
+@pytest.mark.parametrize("n,T", [(40, 1), (40, 2), (8193, 3), (8193, 4)])
+def test_rollout_left_to_the_library(n, T):
+    """Around the steps and envs from which a rollout is one launch: two calls in a
+    row against the same steps one by one, with the frames of every step in one slot."""
+    import torch
+    from paper_2605_19926_amd import jx
+    cfg = W.env_cfg(obs_h=64, obs_w=44, episode_cap=3, side=9)
+    got = []
+    for graph in (True, False):
+        env = jx.Env(W.seeds(43, n), cfg)
+        env.reset()
+        a = torch.from_numpy(W.actions(43, T, n, 6)).to(env.dev)
+        obs = env.new_obs()
+        rew, done = torch.zeros((T, n), device=env.dev), torch.zeros((T, n), dtype=torch.uint8, device=env.dev)
+        for _ in range(2):
+            env.rollout(a, obs, rew, done, T, obs_stride=0, graph=graph)
+        torch.cuda.synchronize()
+        got.append((obs, rew, done, env.get_state_bytes()))
+        env.close()
+    assert _same(*got)
