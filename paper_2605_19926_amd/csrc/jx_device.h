@@ -215,8 +215,8 @@ struct Bfs {
   M unreached;  // passable tiles the search did not reach
 };
 // Search over the passable mask until the frontier empties.  A reset's time is
-// this serial chain (a 32-side maze has 100 to 300 levels, a 64-side one up to
-// about 1000, and a key-door reset searches three times), and one wave's chain
+// this serial chain (a loop-free 32-side maze has some 230 levels, a 64-side one
+// 800, and a key-door reset searches three times), and one wave's chain
 // makes a whole per-step launch end late.  So a level is 7 VALU instructions
 // with 32-bit rows and 15 with 64-bit rows, and the wave asks only every fourth
 // level whether the search has ended.  Against lane shuffles through LDS on
@@ -284,6 +284,181 @@ __device__ __forceinline__ M row_masks(const uint8_t* lmap, uint32_t* lbits, int
   return m;
 }
 
+// ---- the lattice of a maze -------------------------------------------------------
+// A maze's floor lies on rooms (odd row, odd column) and separators between two of
+// them; its pillars (even, even) are walls.  Sets of such tiles take 32-bit words
+// where tile rows take 64: lane k holds rooms r of row 2k + 1 (bit c: column 2c +
+// 1), separators e right of them and s below them.  Levels alternate between rooms
+// and separators, so a search takes two at a time: 11 VALU instructions where two
+// levels of 64-bit rows take 30.
+struct Lattice {
+  uint32_t r, e, s;
+};
+__device__ __forceinline__ bool lattice_any(const Lattice& a) { return wave_any((a.r | a.e | a.s) != 0u); }
+__device__ __forceinline__ Lattice lattice_tile(int id, const TileDiv& td, int lane) {
+  const int y = td.row(id), x = td.col(id);
+  const uint32_t b = lane == ((y - 1) >> 1) ? 1u << (((x - 1) >> 1) & 31) : 0u;
+  return {(y & 1) && (x & 1) ? b : 0u, (y & 1) && !(x & 1) ? b : 0u, !(y & 1) && (x & 1) ? b : 0u};
+}
+// Bits 0, 2, 4, ... of v packed, and the reverse.
+__device__ __forceinline__ uint32_t even_bits(uint64_t v) {
+  v &= 0x5555555555555555ull;
+  v = (v | (v >> 1)) & 0x3333333333333333ull;
+  v = (v | (v >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+  v = (v | (v >> 4)) & 0x00FF00FF00FF00FFull;
+  v = (v | (v >> 8)) & 0x0000FFFF0000FFFFull;
+  return (uint32_t)(v | (v >> 16));
+}
+__device__ __forceinline__ uint64_t spread_bits(uint32_t w) {
+  uint64_t v = w;
+  v = (v | (v << 16)) & 0x0000FFFF0000FFFFull;
+  v = (v | (v << 8)) & 0x00FF00FF00FF00FFull;
+  v = (v | (v << 4)) & 0x0F0F0F0F0F0F0F0Full;
+  v = (v | (v << 2)) & 0x3333333333333333ull;
+  return (v | (v << 1)) & 0x5555555555555555ull;
+}
+__device__ __forceinline__ uint64_t lane_of(uint64_t v, int src) {
+  return ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(v >> 32), src, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)v, src, 64);
+}
+// The lattice of row masks m (lane y: row y); false if some pillar is floor.
+__device__ __forceinline__ bool to_lattice(uint64_t m, int lane, Lattice* out) {
+  const int k = lane & 31;
+  const uint64_t a = lane_of(m, 2 * k + 1), b = k < 31 ? lane_of(m, 2 * k + 2) : 0ull;
+  const bool own = lane < 32;
+  *out = {own ? even_bits(a >> 1) : 0u, own ? even_bits(a >> 2) : 0u, own ? even_bits(b >> 1) : 0u};
+  return !wave_any(own && even_bits(b >> 2) != 0u);
+}
+__device__ __forceinline__ uint64_t from_lattice(const Lattice& a, int lane) {
+  const int k = (lane - 1) >> 1;
+  const uint32_t r = (uint32_t)__shfl((int)a.r, k & 63, 64), e = (uint32_t)__shfl((int)a.e, k & 63, 64),
+                 s = (uint32_t)__shfl((int)a.s, k & 63, 64);
+  if (lane == 0) return 0ull;
+  return (lane & 1) ? (spread_bits(r) << 1) | (spread_bits(e) << 2) : spread_bits(s) << 1;
+}
+// Smallest tile id of the set, -1 if it is empty.
+__device__ __forceinline__ int lattice_first(const Lattice& a, int N) {
+  const uint64_t own = __ballot((a.r | a.e | a.s) != 0u);
+  if (own == 0ull) return -1;
+  const int k = first_bit(own);
+  const uint32_t r = lane_value(a.r, k), e = lane_value(a.e, k), s = lane_value(a.s, k);
+  if ((r | e) == 0u) return (2 * k + 2) * N + 2 * first_bit(s) + 1;
+  const int xr = r ? 2 * first_bit(r) + 1 : 64, xe = e ? 2 * first_bit(e) + 2 : 64;
+  return (2 * k + 1) * N + min(xr, xe);
+}
+// Separators of `in` beside the rooms F, and rooms of `in` beside the separators.
+__device__ __forceinline__ void beside_rooms(uint32_t F, const Lattice& in, uint32_t* e, uint32_t* s) {
+  *e = (F | (F >> 1)) & in.e;
+  *s = (F | lane_next(F)) & in.s;
+}
+__device__ __forceinline__ uint32_t beside_separators(uint32_t e, uint32_t s, const Lattice& in) {
+  return (e | (e << 1) | s | lane_prev(s)) & in.r;
+}
+
+struct LatticeSearch {
+  int level;          // of the farthest tiles
+  int rooms0;         // the first level that holds rooms (0 or 1)
+  Lattice farthest;
+  Lattice unreached;
+  // reached tiles whose level is 2 or 3 more than rooms0, modulo 4: with a tile's
+  // kind, which says its level modulo 2, this tells the levels before and after a
+  // tile's own apart
+  Lattice upper;
+};
+// Search over the passable tiles until nothing is left to reach; every wave
+// reaches the exit, since `unreached` shrinks in every round.
+__device__ LatticeSearch lattice_search(const Lattice& pass, int src, const TileDiv& td, int lane) {
+  const Lattice at = lattice_tile(src, td, lane);
+  LatticeSearch q;
+  Lattice U{pass.r & ~at.r, pass.e & ~at.e, pass.s & ~at.s};
+  Lattice up{0u, 0u, 0u};
+  uint32_t F = at.r;
+  q.rooms0 = 0;
+  if (!wave_any(F != 0u)) {  // from a separator: its rooms come first
+    F = beside_separators(at.e, at.s, U);
+    U.r &= ~F;
+    q.rooms0 = 1;
+    if (!wave_any(F != 0u)) {
+      q.level = 0;
+      q.farthest = at;
+      q.unreached = U;
+      q.upper = up;
+      return q;
+    }
+  }
+  uint32_t F0, e1, s1, F1, e2, s2, F2 = F;
+  int level = q.rooms0 - 4;
+  do {
+    F0 = F2;
+    beside_rooms(F0, U, &e1, &s1);
+    U.e &= ~e1;
+    U.s &= ~s1;
+    F1 = beside_separators(e1, s1, U);
+    U.r &= ~F1;
+    beside_rooms(F1, U, &e2, &s2);
+    U.e &= ~e2;
+    U.s &= ~s2;
+    F2 = beside_separators(e2, s2, U);
+    U.r &= ~F2;
+    up.r |= F1;
+    up.e |= e2;
+    up.s |= s2;
+    level += 4;
+  } while (wave_any(F2 != 0u));
+  if (wave_any((e2 | s2) != 0u)) {
+    level += 3;
+    q.farthest = {0u, e2, s2};
+  } else if (wave_any(F1 != 0u)) {
+    level += 2;
+    q.farthest = {F1, 0u, 0u};
+  } else if (wave_any((e1 | s1) != 0u)) {
+    level += 1;
+    q.farthest = {0u, e1, s1};
+  } else {
+    q.farthest = {F0, 0u, 0u};
+  }
+  q.level = level;
+  q.unreached = U;
+  q.upper = up;
+  return q;
+}
+
+// Tiles at level h of search q on a shortest path from its source to `to`, a tile
+// of its last level (h >= 1): level by level back from `to`.
+__device__ Lattice lattice_back(const LatticeSearch& q, const Lattice& pass, int to, int h, const TileDiv& td, int lane) {
+  Lattice B = lattice_tile(to, td, lane);
+  const Lattice lo{pass.r & ~q.upper.r, pass.e & ~q.upper.e, pass.s & ~q.upper.s};
+  const Lattice hi{pass.r & q.upper.r, pass.e & q.upper.e, pass.s & q.upper.s};
+  // one level down, to the level that is j more than rooms0 modulo 4
+  auto back = [&](int j) {
+    const Lattice& in = j < 2 ? lo : hi;
+    if (j & 1) {
+      uint32_t e, s;
+      beside_rooms(B.r, in, &e, &s);
+      B = {0u, e, s};
+    } else {
+      B = {beside_separators(B.e, B.s, in), 0u, 0u};
+    }
+  };
+  auto any_level = [&](int k) {
+    switch ((k - q.rooms0) & 3) {
+      case 0: back(0); break;
+      case 1: back(1); break;
+      case 2: back(2); break;
+      default: back(3); break;
+    }
+  };
+  int k = q.level;
+  while (k > h && ((k - q.rooms0) & 3)) any_level(--k);
+  for (; k - 4 >= h; k -= 4) {
+    back(3);
+    back(2);
+    back(1);
+    back(0);
+  }
+  while (k > h) any_level(--k);
+  return B;
+}
+
 struct Episode {
   float x, y, th;
   int goal, door, key, nd, dec0, dec1;
@@ -291,8 +466,9 @@ struct Episode {
 
 // Episode reset for episode `e` of the env with layout in `lmap` (0 floor).
 // M: row masks (32 bits where the map is at most 32 wide).
-// ASC: the batch may hold ASCII maps (else that code is compiled out).
-template <bool ASC, typename M>
+// ASC: the batch may hold ASCII maps, LATTICE: maps wider than 16 (else that code
+// is compiled out).
+template <bool ASC, bool LATTICE, typename M>
 __device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint8_t* lmap, uint32_t* lbits, uint64_t seed,
                                  uint32_t e, int lane) {
   const int N = cf.side;
@@ -335,17 +511,42 @@ __device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint
   ep.x = (float)td.col(spawn) + 0.5f;
   ep.y = (float)td.row(spawn) + 0.5f;
 
-  const Bfs<M> b = bfs_all<M>(freem, spawn, td, lane);
-  const int L = b.level;
-  ep.goal = mask_first(b.frontier, N);
+  // goal: the first of the farthest tiles; door: the first tile halfway on a
+  // shortest path to it; key: in the region that the shut door leaves to the spawn
   ep.door = -1;
   ep.key = -1;
   const M spawnb = bit_of<M>(spawn, td, lane);
-  if (cf.key_door && L >= 2) {
-    const int h = L / 2;
-    ep.door = mask_first(bfs_meet<M>(freem, spawn, ep.goal, h, L & 1, td, lane), N);
-    const M pass2 = freem & ~bit_of<M>(ep.door, td, lane);
-    const M region = pass2 & ~bfs_all<M>(pass2, spawn, td, lane).unreached & ~spawnb;
+  M region = 0;
+  bool keyed = false;
+  Lattice floor_;
+  // 64-bit rows search on the lattice where the map is a maze's; 32-bit rows where
+  // a door asks for two more searches (one is over before the lattice is laid out).
+  // A step of 1000 key-door envs of 64 x 64, with one reset: 64-side 72 -> 38 us
+  // (11.5 without it), 33-side 28.7 -> 19.2, 32-side 21.0 -> 18.3; 16-side 16.3 ->
+  // 16.7.
+  if (LATTICE && (sizeof(M) == 8 || (cf.key_door && N > 16)) && to_lattice((uint64_t)freem, lane, &floor_)) {
+    const LatticeSearch q = lattice_search(floor_, spawn, td, lane);
+    ep.goal = lattice_first(q.farthest, N);
+    keyed = cf.key_door && q.level >= 2;
+    if (keyed) {
+      ep.door = lattice_first(lattice_back(q, floor_, ep.goal, q.level / 2, td, lane), N);
+      const Lattice d = lattice_tile(ep.door, td, lane);
+      const Lattice pass2{floor_.r & ~d.r, floor_.e & ~d.e, floor_.s & ~d.s};
+      const Lattice u = lattice_search(pass2, spawn, td, lane).unreached;
+      region = (M)from_lattice({pass2.r & ~u.r, pass2.e & ~u.e, pass2.s & ~u.s}, lane) & ~spawnb;
+    }
+  } else {
+    const Bfs<M> b = bfs_all<M>(freem, spawn, td, lane);
+    const int L = b.level;
+    ep.goal = mask_first(b.frontier, N);
+    keyed = cf.key_door && L >= 2;
+    if (keyed) {
+      ep.door = mask_first(bfs_meet<M>(freem, spawn, ep.goal, L / 2, L & 1, td, lane), N);
+      const M pass2 = freem & ~bit_of<M>(ep.door, td, lane);
+      region = pass2 & ~bfs_all<M>(pass2, spawn, td, lane).unreached & ~spawnb;
+    }
+  }
+  if (keyed) {
     const uint32_t c = mask_count(region);
     ep.key = (c == 0) ? spawn : mask_select(region, sm_draw(s, c), N);
   }
@@ -1160,8 +1361,8 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
     // the LDS of the records that this wave is about to write is scratch here
     // (where two waves cast, each has the half of its own 64 columns)
     uint32_t* lbits = lcol + 128 * part;
-    const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, uint32_t>(cf, td, lmap, lbits, seed, e, lane)
-                                            : episode_reset<ASC, uint64_t>(cf, td, lmap, lbits, seed, e, lane);
+    const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, (MAXN > 16), uint32_t>(cf, td, lmap, lbits, seed, e, lane)
+                                            : episode_reset<ASC, (MAXN > 16), uint64_t>(cf, td, lmap, lbits, seed, e, lane);
     x = n.x;
     y = n.y;
     th = n.th;

@@ -25,6 +25,9 @@ def _interior(kind, side, rng):
     g = np.ones((side, side), np.uint8)
     if kind == "random":
         g[1:-1, 1:-1] = rng.random((side - 2, side - 2)) < 0.35
+    elif kind == "rooms":  # on a maze's lattice, but with dead-end separators and cut-off parts
+        g[1:-1, 1:-1] = rng.random((side - 2, side - 2)) < 0.25
+        g[::2, ::2] = 1
     elif kind == "hall":
         g[1:-1, 1:-1] = 0
     elif kind == "corridor":  # a snake: the longest shortest paths
@@ -73,12 +76,12 @@ def test_maze_resets(side, kind):
     _check_next_episode(W.env_cfg(side=side, obs_h=32, obs_w=32, episode_cap=64, **KINDS[kind]), 12)
 
 
-@pytest.mark.parametrize("kind", ["random", "hall", "corridor", "single"])
-@pytest.mark.parametrize("side", [5, 16, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("kind", ["random", "rooms", "hall", "corridor", "single"])
+@pytest.mark.parametrize("side", [5, 16, 31, 32, 33, 34, 47, 63, 64])
 def test_resets_on_loaded_maps(side, kind):
     rng = np.random.default_rng(side)
     cfg = W.env_cfg(side=side, obs_h=32, obs_w=32, episode_cap=64, key_door=1, max_decor=2)
-    _check_next_episode(cfg, 8, [_interior(kind, side, rng) for _ in range(8)])
+    _check_next_episode(cfg, 16, [_interior(kind, side, rng) for _ in range(16)])
 
 
 @pytest.mark.parametrize("text,side", [(W.MAP16, 16), (W.MAP16, 33), (W.MAP16.replace("G", "."), 16),
