@@ -318,7 +318,8 @@ jx_status jx_make_layout(uint64_t seed, const jx_env_cfg* cfg, uint8_t* grid_hos
  * wait in FIFO order.  All functions are thread-safe.  For latency two of the
  * server's threads poll rather than sleep: the scheduler for up to 1 ms when
  * the device falls idle, the completion thread every 2 us while launches are
- * in flight, so a busy server keeps up to two host cores busy.
+ * in flight, so a busy server keeps up to two host cores busy.  A caller in
+ * jx_server_wait polls its request for up to 0.1 ms before it sleeps.
  * ------------------------------------------------------------------------- */
 typedef struct jx_server jx_server;
 
