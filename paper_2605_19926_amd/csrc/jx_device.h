@@ -158,11 +158,14 @@ __device__ __forceinline__ uint32_t sm_draw(uint64_t& s, uint32_t n) {
 // Row and column of a tile id (below 4096) on an N-wide map (N from 5 to 64) by
 // one multiplication: m = floor(2^18 / N) + 1 exceeds 2^18 / N by at most 1, so
 // id * m / 2^18 exceeds id / N by at most id / 2^18 < 1 / N (4095 * 64 < 2^18),
-// which never reaches the next integer.
+// which never reaches the next integer.  The quotient 2^18 / N itself comes from
+// the hardware reciprocal: a quarter of its smallest fraction 1 / N is added, which
+// is five times the error of the reciprocal (1 ulp) and the product.
 struct TileDiv {
   int N;
   uint32_t m;
-  __device__ __forceinline__ explicit TileDiv(int n) : N(n), m((1u << 18) / (uint32_t)n + 1u) {}
+  __device__ __forceinline__ explicit TileDiv(int n)
+      : N(n), m((uint32_t)(262144.25f * __builtin_amdgcn_rcpf((float)n)) + 1u) {}
   __device__ __forceinline__ int row(int id) const { return (int)(((uint32_t)id * m) >> 18); }
   __device__ __forceinline__ int col(int id) const { return id - row(id) * N; }
 };
@@ -892,6 +895,7 @@ __device__ void render_columns(const DevCfg& cf, const TileDiv& td, const DevIo&
     sHS[j] = (float)H * 0.25f * inv;
   }
 
+  seen = uniform_u(seen);
   const int ix0 = (int)floorf(x), iy0 = (int)floorf(y);
   const float halfH = (float)(H >> 1);
   const float INF = __builtin_huge_valf();
@@ -899,8 +903,9 @@ __device__ void render_columns(const DevCfg& cf, const TileDiv& td, const DevIo&
   const LdsBytes shutq = map0 + shut;
   const uint32_t last = (uint32_t)(N * N - 1);
   // hit / K by one multiplication (hit below 4096, K at most 8: hit times the
-  // excess of km over 2^16 / K stays below 2^16)
-  const uint32_t km = 65535u / (uint32_t)K + 1u;
+  // excess of km over 2^16 / K stays below 2^16); km = floor(65535 / K) + 1, half of
+  // the smallest fraction added as in TileDiv
+  const uint32_t km = (uint32_t)(65535.5f * __builtin_amdgcn_rcpf((float)K)) + 1u;
   for (int col = col0; col < W; col += hop) {
     // The ray components are formed in double and rounded once: dir and the
     // column's offset along `right` can nearly cancel, and a float sum would
@@ -1229,17 +1234,13 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
   const int env = in.env;
   const int N = cf.side;
   const TileDiv td(N);
-  if (STAGE) stage_map<MAXN>(in, lane, lmap);
   float x = in.x, y = in.y, th = in.th;
   uint32_t t = in.t, ep = in.ep;
   int goal = in.goal, door = in.door, key = in.key;
   int dec0 = in.dec0, dec1 = in.dec1;
-  uint32_t fl = uniform_u(in.fl);
   uint32_t doors = in.doors;
-  int nd = (int)uniform_u((uint32_t)in.nd);
   a = (int)uniform_u((uint32_t)a);
   const uint64_t seed = in.seed;
-  wave_sync();
 
   // Every value here is uniform across the wave.  The branches ask ballots, so
   // they stay scalar.  (Moving the state itself into scalar registers as well
@@ -1266,6 +1267,11 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
   } else if (STAGE && mode != MODE_RESET) {
     sincos((double)th, &dsn, &dcs);
   }
+  // (the map's loads are still under way during the sincos)
+  if (STAGE) stage_map<MAXN>(in, lane, lmap);
+  uint32_t fl = uniform_u(in.fl);
+  int nd = (int)uniform_u((uint32_t)in.nd);
+  wave_sync();
   if (mode == MODE_STEP) {
     if (a >= cf.n_actions) ev |= EV_INVALID;
     else prev = (uint32_t)a;
@@ -1454,17 +1460,17 @@ __device__ __forceinline__ void process_env(const DevState& S, const DevIo& io, 
                             const uint32_t* lclr, const uint32_t* lcvt, uint32_t* lcol, int part = 0,
                             int parts = 1, bool live = true) {
   EnvOut o{};
-  if (live) {
+  int casters = 1;
+  if (parts > 1 && live) {  // (one wave per env does not wait for this)
     const DevCfg& cf = S.uniform ? S.ucfg : S.cfgs[S.cfg_idx[env]];
-    const int casters = parts > 1 && cf.obs_w > 64 ? 2 : 1;
-    if (part < casters) {
-      EnvIn<MAXN> in;
-      load_env<MAXN>(S, io.mode == MODE_STEP ? io.act : nullptr, env, lane, in);
-      produce_env<MAXN, true, ASC>(in, io, (int)in.act, lane, lmap, lclr, lcol, o, part, casters);
-    } else {
-      o.W = cf.obs_w;
-      o.H = cf.obs_h;
-    }
+    casters = cf.obs_w > 64 ? 2 : 1;
+    o.W = cf.obs_w;
+    o.H = cf.obs_h;
+  }
+  if (live && part < casters) {
+    EnvIn<MAXN> in;
+    load_env<MAXN>(S, io.mode == MODE_STEP ? io.act : nullptr, env, lane, in);
+    produce_env<MAXN, true, ASC>(in, io, (int)in.act, lane, lmap, lclr, lcol, o, part, casters);
   }
   if (parts > 1) __syncthreads();
   if (!live) return;
