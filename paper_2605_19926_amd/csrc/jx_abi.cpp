@@ -360,7 +360,7 @@ jx_status jx_render(jx_ctx* c, uint8_t* obs, jx_col_debug* dbg) {
 
 size_t jx_state_bytes(const jx_ctx* c) {
   if (!c || c->n < 0) return 0;
-  return (size_t)c->L.spare;
+  return (size_t)c->L.rdesc;
 }
 
 jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_fields) {
@@ -395,7 +395,7 @@ jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_
              {"obs_offset", L.obs_off, 8, (int64_t)n + 1},
              {"order", L.order, 4, n},
              {"cfgs", L.cfgs, (int)sizeof(DevCfg), (int64_t)c->cfgs.size()},
-             {"maps", L.maps, 1, L.spare - L.maps}};
+             {"maps", L.maps, 1, L.rdesc - L.maps}};
   const int total = (int)(sizeof(all) / sizeof(all[0]));
   if (n_fields) *n_fields = total;
   if (!f) return JX_OK;
@@ -413,9 +413,9 @@ jx_status jx_state_layout(const jx_ctx* c, jx_field* f, int32_t cap, int32_t* n_
 jx_status jx_get_state(const jx_ctx* c, void* host, size_t bytes) {
   jx_status st = check_ready(c);
   if (st) return st;
-  if (!host || bytes < (size_t)c->L.spare) return set_error(JX_EINVAL, "host buffer too small");
+  if (!host || bytes < (size_t)c->L.rdesc) return set_error(JX_EINVAL, "host buffer too small");
   HIPCHK(hipSetDevice(c->device));
-  HIPCHK(hipMemcpyAsync(host, c->ws, (size_t)c->L.spare, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipMemcpyAsync(host, c->ws, (size_t)c->L.rdesc, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return JX_OK;
 }
@@ -423,11 +423,11 @@ jx_status jx_get_state(const jx_ctx* c, void* host, size_t bytes) {
 jx_status jx_set_state(jx_ctx* c, const void* host, size_t bytes) {
   jx_status st = check_ready(c);
   if (st) return st;
-  if (!host || bytes < (size_t)c->L.spare) return set_error(JX_EINVAL, "state image too small");
+  if (!host || bytes < (size_t)c->L.rdesc) return set_error(JX_EINVAL, "state image too small");
   const uint8_t* b = (const uint8_t*)host;
   WsHeader h;
   std::memcpy(&h, b + c->L.hdr, sizeof(h));
-  if (h.magic != kStateMagic || h.n_envs != c->n || h.state_bytes != c->L.spare ||
+  if (h.magic != kStateMagic || h.n_envs != c->n || h.state_bytes != c->L.rdesc ||
       h.n_cfgs != (int32_t)c->cfgs.size())
     return set_error(JX_EINVAL, "state image does not match this context");
   if (std::memcmp(b + c->L.cfgs, c->dev_cfgs.data(), sizeof(DevCfg) * c->dev_cfgs.size()) != 0 ||
@@ -437,7 +437,7 @@ jx_status jx_set_state(jx_ctx* c, const void* host, size_t bytes) {
   // every index the kernels dereference must be in range
   st = check_state_image(b, c->L, c->n, c->cfgs, c->cfg_idx);
   if (st) return st;
-  std::vector<uint8_t> img(b, b + c->L.spare);
+  std::vector<uint8_t> img(b, b + c->L.rdesc);
   WsHeader* hh = (WsHeader*)(img.data() + c->L.hdr);
   hh->queue = 0;
   hh->exited = 0;
@@ -553,7 +553,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
     if (chosen) jx_get_launch(c, chosen);
     return JX_OK;
   }
-  const size_t total = (size_t)c->L.spare;  // the state image
+  const size_t total = (size_t)c->L.rdesc;  // the state image
   const int64_t ob = c->obs_off.back();
   const int n = c->n;
   uint8_t* snap = nullptr;

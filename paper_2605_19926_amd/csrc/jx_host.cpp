@@ -124,7 +124,7 @@ Layout make_layout(int n, int n_cfgs, int64_t maps_bytes) {
   L.cfgs = take((int64_t)sizeof(DevCfg) * std::max(n_cfgs, 1));
   L.maps = take(std::max<int64_t>(maps_bytes, 16));
   // after the state image: the rollout descriptor (scratch, not state)
-  L.spare = take(kSpareBytes);
+  L.rdesc = take(kSpareBytes);
   L.queues = take(4 * kQueueWords);
   L.total = o;
   return L;
@@ -209,7 +209,7 @@ jx_status build_image(int n, const uint64_t* seeds, const jx_env_cfg* cfgs, int 
   WsHeader* h = (WsHeader*)(b + L.hdr);
   h->magic = kStateMagic;
   h->n_envs = n;
-  h->state_bytes = L.spare;
+  h->state_bytes = L.rdesc;
   h->n_cfgs = n_cfgs;
   obs_off->assign(n + 1, 0);
   for (int i = 0; i < n; ++i) {
@@ -290,7 +290,7 @@ jx_status check_state_image(const uint8_t* b, const Layout& L, int n, const std:
     std::memcpy(&moff, b + L.map_off + 4 * i, 4);
     bool ok = std::isfinite(x) && std::isfinite(y) && std::isfinite(th) && x >= 0.f && y >= 0.f &&
               x < (float)N && y < (float)N && nd <= kMaxDecor && b[L.flags + i] <= 31 &&
-              moff + (uint64_t)NN <= (uint64_t)(L.spare - L.maps);
+              moff + (uint64_t)NN <= (uint64_t)(L.rdesc - L.maps);
     for (int k = 0; k < 5; ++k) ok = ok && ids[k] >= -1 && ids[k] < NN;
     for (int k = 0; k < 3; ++k) {
       int32_t ak;

@@ -117,13 +117,14 @@ struct ServeItem {
   int32_t env;
 };
 
-// Workspace layout: byte offsets of every array.
+// Workspace layout: byte offsets of every array (rdesc: the spare bytes behind the
+// maps, where the state image ends).
 struct Layout {
   int64_t hdr, x, y, th, t, ep, goal, door, key, decor, akey, doors, flags, events, ndecor, invalid, seed,
-      cfg_idx, map_off, obs_off, order, spare, queues, cfgs, maps, total;
+      cfg_idx, map_off, obs_off, order, rdesc, queues, cfgs, maps, total;
 };
 
-// Launch entry points implemented in jx_kernels.hip.
+// Launch entry points implemented in jx_kernels.hip, jx_roll.hip and jx_roll_narrow.hip.
 struct LaunchCfg {
   int32_t form, waves_per_group, groups_per_cu, store_mode;
   int32_t waves_per_env = 1;  // plain form: waves sharing one env (1, 2, 4; at most waves_per_group)
