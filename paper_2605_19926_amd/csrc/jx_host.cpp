@@ -123,7 +123,7 @@ Layout make_layout(int n, int n_cfgs, int64_t maps_bytes) {
   L.order = take(4 * nn);
   L.cfgs = take((int64_t)sizeof(DevCfg) * std::max(n_cfgs, 1));
   L.maps = take(std::max<int64_t>(maps_bytes, 16));
-  // after the state image: the rollout descriptor (scratch, not state)
+  // after the state image
   L.rdesc = take(kSpareBytes);
   L.queues = take(4 * kQueueWords);
   L.total = o;
