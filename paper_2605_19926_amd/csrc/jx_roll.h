@@ -169,16 +169,17 @@ __global__ __launch_bounds__(64 * WPB, OCC) void k_roll(DevState S, RollIo r) {
   }
 }
 
+// lds: bytes of LDS asked for beside the kernel's own, to bound the groups per CU
 template <int MAXN, bool ASC, int FMT, int OCC>
-int launch_roll_n(const DevState& s, const RollIo& r, int wpb, int groups, hipStream_t st) {
+int launch_roll_n(const DevState& s, const RollIo& r, int wpb, int groups, int lds, hipStream_t st) {
   if constexpr (FMT != 0) {
-    hipLaunchKernelGGL((k_roll<MAXN, kFmtWaves, ASC, FMT, OCC>), dim3(groups), dim3(64 * kFmtWaves), 0, st, s, r);
+    hipLaunchKernelGGL((k_roll<MAXN, kFmtWaves, ASC, FMT, OCC>), dim3(groups), dim3(64 * kFmtWaves), lds, st, s, r);
   } else {
     switch (wpb) {
-      case 1: hipLaunchKernelGGL((k_roll<MAXN, 1, ASC, 0, OCC>), dim3(groups), dim3(64), 0, st, s, r); break;
-      case 2: hipLaunchKernelGGL((k_roll<MAXN, 2, ASC, 0, OCC>), dim3(groups), dim3(128), 0, st, s, r); break;
-      case 4: hipLaunchKernelGGL((k_roll<MAXN, 4, ASC, 0, OCC>), dim3(groups), dim3(256), 0, st, s, r); break;
-      case 8: hipLaunchKernelGGL((k_roll<MAXN, 8, ASC, 0, OCC>), dim3(groups), dim3(512), 0, st, s, r); break;
+      case 1: hipLaunchKernelGGL((k_roll<MAXN, 1, ASC, 0, OCC>), dim3(groups), dim3(64), lds, st, s, r); break;
+      case 2: hipLaunchKernelGGL((k_roll<MAXN, 2, ASC, 0, OCC>), dim3(groups), dim3(128), lds, st, s, r); break;
+      case 4: hipLaunchKernelGGL((k_roll<MAXN, 4, ASC, 0, OCC>), dim3(groups), dim3(256), lds, st, s, r); break;
+      case 8: hipLaunchKernelGGL((k_roll<MAXN, 8, ASC, 0, OCC>), dim3(groups), dim3(512), lds, st, s, r); break;
       default: return -1;
     }
   }

@@ -41,8 +41,8 @@ int launch_proll_n(const DevState& s, const RollIo& r, int wpb, int groups, uint
 
 template <int MAXN, bool ASC, int FMT>
 struct RollL {
-  static int run(const DevState& s, const RollIo& r, int wpb, int groups, hipStream_t st) {
-    return launch_roll_n<MAXN, ASC, FMT, 1>(s, r, wpb, groups, st);
+  static int run(const DevState& s, const RollIo& r, int wpb, int groups, int lds, hipStream_t st) {
+    return launch_roll_n<MAXN, ASC, FMT, 1>(s, r, wpb, groups, lds, st);
   }
 };
 
@@ -81,7 +81,7 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
   const int wpb = wpe > 1 ? wpe : s.obs_fmt != 0 ? kFmtWaves : lc.waves_per_group;
   // wpe waves per env while they fit on the chip, else a stride.
   int groups = (int)(((int64_t)s.n * wpe + wpb - 1) / wpb);
-  int per_cu = 16 / wpb;
+  const int per_cu = 16 / wpb;
   bool dense = false;
   if (wpe == 1 && s.obs_fmt == 0 && !s.any_ascii) {
     // Byte frames of generated mazes.  Frames below 8 KB wait for the casting:
@@ -93,11 +93,26 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
     // (The other kernel lets in 12 waves per CU, or one 8-wave workgroup.)
     dense = frames_bytes < (int64_t)s.n * 8192 && s.n > (wpb == 8 ? 8 : 12) * n_cu;
   }
+  int lds = 0;
+  if (wpe == 1 && wpb == 4 && !s.any_ascii && max_side <= 32 && s.obs_fmt <= 3 && s.n > 12 * n_cu &&
+      frames_bytes >= (int64_t)s.n * 8192) {
+    // Groups of 4 waves whose registers (bytes, NHWC, sides to 32) let 12 waves onto
+    // a CU, and frames that wait for the memory: 8 waves per CU write more evenly
+    // than 12 and a rest.  LDS that nobody reads keeps the third group out (its own
+    // is at most 10.4 KB of the 64 KB a group may ask for), so that a CU still takes
+    // the next group when one ends.  us for 24 steps with 12 and 8 waves: 4096 envs of
+    // 64 x 64 bytes 261 and 247, NCHW 271 and 254, bfloat16 475 and 467; 8192 of 84 x 84
+    // bytes 892 and 846, NCHW 927 and 878, bfloat16 1720 and 1645.  Up to 12 per CU
+    // all run at once (3072 of 64 x 64 bytes: 188 and 201).  Bytes in NHWC keep 12
+    // where 8 fill their last round no better (5000 of 64 x 64: 305 and 314).
+    const int64_t r8 = (s.n + 8 * n_cu - 1) / (8 * n_cu) * 8, r12 = (s.n + 12 * n_cu - 1) / (12 * n_cu) * 12;
+    if (s.obs_fmt != 0 || r8 < r12) lds = 49 * 1024;
+  }
   const int most = n_cu * (per_cu > 0 ? per_cu : 1);
   if (groups > most) groups = most;
   if (wpe > 1) return launch_roll_split(s, max_side, r, groups, wpe, st);
   if (dense) return launch_roll_dense(s, max_side, r, wpb, groups, st);
-  return by_shape<RollL>(s, max_side, r, wpb, groups, st);
+  return by_shape<RollL>(s, max_side, r, wpb, groups, lds, st);
 }
 
 }  // namespace jx

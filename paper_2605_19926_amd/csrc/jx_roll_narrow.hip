@@ -84,9 +84,9 @@ int launch_roll_split(const DevState& s, int max_side, const RollIo& r, int grou
 }
 
 int launch_roll_dense(const DevState& s, int max_side, const RollIo& r, int wpb, int groups, hipStream_t st) {
-  if (max_side <= 16) return launch_roll_n<16, false, 0, 4>(s, r, wpb, groups, st);
-  if (max_side <= 32) return launch_roll_n<32, false, 0, 4>(s, r, wpb, groups, st);
-  return launch_roll_n<64, false, 0, 4>(s, r, wpb, groups, st);
+  if (max_side <= 16) return launch_roll_n<16, false, 0, 4>(s, r, wpb, groups, 0, st);
+  if (max_side <= 32) return launch_roll_n<32, false, 0, 4>(s, r, wpb, groups, 0, st);
+  return launch_roll_n<64, false, 0, 4>(s, r, wpb, groups, 0, st);
 }
 
 }  // namespace jx

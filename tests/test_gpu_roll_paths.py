@@ -109,3 +109,25 @@ def test_rollout_left_to_the_library(n, T):
         got.append((obs, rew, done, env.get_state_bytes()))
         env.close()
     assert _same(*got)
+
+
+@pytest.mark.parametrize("w", [64, 68, 84, 88, 128])
+def test_float32_rows_around_the_wave(w):
+    """NHWC float32 rows of one wave, and of more in one pass or two."""
+    cfg = W.env_cfg(obs_h=18, obs_w=w, episode_cap=9, obs_dtype=2, **TREE)
+    byte = W.env_cfg(obs_h=18, obs_w=w, episode_cap=9, **TREE)
+    want = _run(byte, 6, 11, ONE, False)
+    frames = (want[0].cpu().numpy().astype(np.float32) / np.float32(255)).view(np.uint8)
+    for launch in (ONE, dict(waves_per_group=4, waves_per_env=2), dict(waves_per_group=4, waves_per_env=4)):
+        for fused in (False, True):
+            got = _run(cfg, 6, 11, launch, fused)
+            assert np.array_equal(got[0].cpu().numpy(), frames) and _same(got[1:4], want[1:4]), (launch, fused)
+
+
+@pytest.mark.parametrize("layout,dtype", [(0, 0), (1, 0), (0, 1), (0, 2)])
+@pytest.mark.parametrize("n,side", [(3072, 16), (3073, 16), (4097, 32)])
+def test_rollouts_of_two_waves_per_simd(n, side, layout, dtype):
+    """Around the batch from which groups of 4 waves hold back the CU's third group."""
+    cfg = W.env_cfg(side=side, obs_h=54, obs_w=52, episode_cap=5, obs_layout=layout, obs_dtype=dtype, goal_sprite=1)
+    want = _run(cfg, n, 6, ONE, False)
+    assert _same(_run(cfg, n, 6, dict(waves_per_group=4), True), want)
