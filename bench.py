@@ -452,11 +452,11 @@ def main() -> int:
     episodes_timed = int(env.get_state()["episode"].astype(np.int64).sum()) - ep_before
     sec = ms / 1e3
     rate = n * K / sec
-    # The fused form runs one kernel per ring chunk (up to 128 steps); the
-    # other forms run one kernel per step.  Layout and state move once per
+    # The fused form, and the graph flag that takes it too, run one kernel per ring
+    # chunk (up to 128 steps); the other forms run one kernel per step.  Layout and state move once per
     # launch, frames, actions, rewards and dones once per step.
     chunks = plan(Wu, K)
-    launches = len(chunks) if args.form == "fused" else K
+    launches = len(chunks) if args.form in ("fused", "graph") else K
     ab = algorithmic_bytes(cfg, K // launches)
     total_bytes = n * (K * ab["per_step"] + launches * ab["per_launch_once"])
     per_launch = total_bytes / launches
@@ -632,7 +632,7 @@ def main() -> int:
                    "obs_ring_slots": slots, "global_batch": n},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_roll" if args.form == "fused" else
+                     "kernel": "k_roll" if args.form in ("fused", "graph") else
                                {"persistent": "k_persist", "pipeline": "k_pipe"}.get(args.form, "k_plain"),
                      "launches": launches, "steps_per_launch": K / launches,
                      "bytes_per_launch": per_launch,
