@@ -62,6 +62,14 @@ static LaunchCfg step_launch(const jx_ctx* c) {
   return l;
 }
 
+// A mapping that somebody chose: the plain form shares an env among no more waves
+// than the group was given (the other forms have no such count).
+static LaunchCfg mapping(int form, int waves_per_group, int groups_per_cu, int store_mode, int waves_per_env = 1) {
+  LaunchCfg l{form, waves_per_group, groups_per_cu, store_mode, waves_per_env};
+  if (form == JX_FORM_PLAIN) l.most_waves_per_env = std::min(4, waves_per_group);
+  return l;
+}
+
 // Enqueues one step/render launch on the context's stream.
 static jx_status launch_or_fail(jx_ctx* c, const DevIo& io) {
   int rc = launch_batch(c->S, io, step_launch(c), c->max_side, c->max_w, c->obs_off.back(), c->n_cu, c->seq,
@@ -462,7 +470,7 @@ jx_status jx_set_launch(jx_ctx* c, const jx_launch* l) {
   if (wpe > 1 && l->form != JX_FORM_PLAIN) return set_error(JX_EINVAL, "waves_per_env > 1 needs the plain form");
   if (wpe > w) return set_error(JX_EINVAL, "waves_per_env must not exceed waves_per_group");
   c->launch_chosen = true;
-  c->launch = LaunchCfg{l->form, w, std::max(1, l->groups_per_cu), l->store_mode, wpe};
+  c->launch = mapping(l->form, w, std::max(1, l->groups_per_cu), l->store_mode, wpe);
   return JX_OK;
 }
 
@@ -548,7 +556,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   const std::string key = tune_key(c);
   LaunchCfg hit{};
   if (cache_lookup(cache_path, key, &hit)) {
-    c->launch = hit;
+    c->launch = mapping(hit.form, hit.waves_per_group, hit.groups_per_cu, hit.store_mode, hit.waves_per_env);
     c->launch_chosen = true;
     if (chosen) jx_get_launch(c, chosen);
     return JX_OK;
@@ -577,16 +585,16 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
 
   std::vector<LaunchCfg> cands;
   for (int w : {1, 2, 4, 8})
-    for (int s : {0, 1}) cands.push_back(LaunchCfg{0, w, 1, s});
+    for (int s : {0, 1}) cands.push_back(mapping(0, w, 1, s));
   // several waves per env (small batches of large frames)
   for (int w : {4, 8})
-    for (int e : {2, 4}) cands.push_back(LaunchCfg{0, w, 1, 0, e});
+    for (int e : {2, 4}) cands.push_back(mapping(0, w, 1, 0, e));
   for (int w : {1, 2, 4})
     for (int g : {2, 4, 8})
-      for (int s : {0, 1}) cands.push_back(LaunchCfg{1, w, g, s});
+      for (int s : {0, 1}) cands.push_back(mapping(1, w, g, s));
   for (int p : {1, 2, 4})
     for (int g : {1, 2, 4})
-      for (int s : {0, 1}) cands.push_back(LaunchCfg{2, p, g, s});
+      for (int s : {0, 1}) cands.push_back(mapping(2, p, g, s));
   const LaunchCfg keep = c->launch;
   const bool keep_chosen = c->launch_chosen;
   c->launch_chosen = true;

@@ -196,17 +196,7 @@ int launch_batch(const DevState& s, const DevIo& io,
   // steps and renders that write frames (resets and debug records take one).
   if (lc.form == 0 || s.obs_fmt != 0) {
     const bool frames = io.mode != MODE_RESET && io.obs != nullptr && io.dbg == nullptr;
-    int wpe = frames ? lc.waves_per_env : 1, wpg = wpb;
-    // Where the caller asks for one wave per env and the batch leaves most of the
-    // chip idle, frames of 16 KB and more take four: one wave would write each
-    // longer than the rest of the step lasts.  us per step with 1 and 4 waves: 256
-    // envs of 64 x 64 float32 12.7, 10.8, 768 of them 18.0, 17.9, 1024 20.4, 20.6;
-    // with two casting waves 1024 of 128 x 128 bytes 16.2, 15.2; 128 of 128 x 128
-    // float32 26.4, 15.8; 768 of 84 x 84 bytes 21.3, 21.0.
-    if (frames && wpe == 1 && frames_bytes >= (int64_t)s.n * 16384 && s.n <= (max_w > 64 ? 4 : 3) * n_cu) {
-      wpe = 4;
-      if (wpg < 4) wpg = 4;
-    }
+    const int wpe = step_waves_per_env(lc, frames, s.n, frames_bytes, max_w, n_cu), wpg = wpb < wpe ? wpe : wpb;
     return by_shape<PlainL>(s, max_side, io, wpg, wpe, st);
   }
   if (lc.form == 2) {

@@ -70,14 +70,7 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
     if (groups < 1) groups = 1;
     return by_shape_f<PRollL, 0>(s, max_side, r, wpb, groups, seq, st);
   }
-  // Waves per env where the caller asks for one.  A batch that leaves the chip
-  // idle pays the step's latency, which the writing waves take a third off, and
-  // large frames more; the casting of two waves' envs is not slower up to 6
-  // waves per CU.  us per step with 1, 2, 4 waves: 256 envs of 64 x 64 bytes 3.80,
-  // 2.78, 2.74; 512 of 84 x 84 key-door 5.78, 4.58, 3.62; 512 of 128 x 128 float32
-  // 28.4, 22.0, 21.9; 1024 of 64 x 64 bytes 3.92, 3.13, 3.13, bfloat16 6.07, 5.16,
-  // 5.89; 1536 of 64 x 64 bytes 4.34, 3.94, 5.06; 2048 of 84 x 84 9.46, 9.91, 10.4.
-  const int wpe = lc.waves_per_env > 1 ? lc.waves_per_env : s.n <= 2 * n_cu ? 4 : s.n <= 6 * n_cu ? 2 : 1;
+  const int wpe = fused_waves_per_env(lc, s.n, n_cu);
   const int wpb = wpe > 1 ? wpe : s.obs_fmt != 0 ? kFmtWaves : lc.waves_per_group;
   // wpe waves per env while they fit on the chip, else a stride.
   int groups = (int)(((int64_t)s.n * wpe + wpb - 1) / wpb);

@@ -1,0 +1,91 @@
+// The launch mappings that the context hands to the kernels, on the CPU: the
+// library's host code over fake_hip.h, whose launches are recorded.
+#include "fake_hip.h"
+
+#include "../../paper_2605_19926_amd/csrc/jx_abi.cpp"
+
+namespace {
+
+struct Ctx {
+  jx_ctx* c = nullptr;
+  std::vector<uint8_t> ws, obs;
+  std::vector<uint8_t> act, done;
+  std::vector<float> rew;
+  int n;
+  jx_env_cfg cfg{};
+  Ctx(int n_envs, int px, int T = 8) : n(n_envs) {
+    cfg.side = 8;
+    cfg.n_colors = 8;
+    cfg.goal_sprite = 1;
+    cfg.obs_h = cfg.obs_w = px;
+    cfg.fov_deg = 60.f;
+    cfg.n_actions = 6;
+    cfg.episode_cap = 64;
+    cfg.move = 0.1f;
+    cfg.turn = 0.2f;
+    cfg.pickup_radius = 0.3f;
+    cfg.r_goal = 1.f;
+    const size_t bytes = jx_workspace_bytes(n, &cfg, 1, nullptr);
+    ws.resize(bytes + 256);
+    uint8_t* base = ws.data() + (256 - ((uintptr_t)ws.data() & 255)) % 256;
+    std::vector<uint64_t> seeds(n);
+    for (int i = 0; i < n; ++i) seeds[i] = (uint64_t)i;
+    CHECK(jx_create(&c, 0, nullptr, base, bytes) == JX_OK, "create: %s", jx_last_error());
+    CHECK(jx_reset(c, n, seeds.data(), &cfg, 1, nullptr, nullptr) == JX_OK, "reset: %s", jx_last_error());
+    act.resize((size_t)T * n);
+    done.resize((size_t)T * n);
+    rew.resize((size_t)T * n);
+    obs.resize((size_t)jx_obs_bytes(c) + 64);
+  }
+  ~Ctx() { jx_destroy(c); }
+  uint8_t* frames() { return obs.data() + (64 - ((uintptr_t)obs.data() & 63)) % 64; }
+  void set(int form, int wpg, int gpc, int store, int wpe) {
+    const jx_launch l{form, wpg, gpc, store, wpe};
+    CHECK(jx_set_launch(c, &l) == JX_OK, "set_launch: %s", jx_last_error());
+  }
+  fake::Launch step() {
+    CHECK(jx_step(c, act.data(), frames(), rew.data(), done.data(), nullptr) == JX_OK, "step: %s", jx_last_error());
+    return fake::launches.back();
+  }
+  fake::Launch rollout(int flags, int T = 8) {
+    CHECK(jx_rollout(c, T, act.data(), frames(), 0, rew.data(), done.data(), nullptr, flags) == JX_OK, "rollout: %s",
+          jx_last_error());
+    return fake::launches.back();
+  }
+};
+
+// One wave per env is what a group of one wave gives; larger groups and a mapping
+// left to the library take more on a batch that leaves the chip idle.
+void check_waves_per_env() {
+  for (int n : {1, 128, 512, 700}) {
+    Ctx x(n, 128);
+    const int fused = n <= 512 ? 4 : 2;
+    CHECK(x.step().waves_per_env == 4, "left to the library: step n %d", n);
+    CHECK(x.rollout(JX_ROLLOUT_FUSED).waves_per_env == fused, "left to the library: fused n %d", n);
+    for (int wpg : {1, 2, 4, 8}) {
+      x.set(0, wpg, 1, 0, 1);
+      CHECK(x.step().waves_per_env == (wpg >= 4 ? 4 : 1), "groups of %d: step n %d", wpg, n);
+      CHECK(x.rollout(JX_ROLLOUT_FUSED).waves_per_env == std::min(wpg, fused), "groups of %d: fused n %d", wpg, n);
+      CHECK(x.rollout(JX_ROLLOUT_GRAPH).waves_per_env == std::min(wpg, fused), "groups of %d: graph n %d", wpg, n);
+      for (int wpe : {2, 4})
+        if (wpe <= wpg) {
+          x.set(0, wpg, 1, 0, wpe);
+          CHECK(x.step().waves_per_env == wpe && x.rollout(JX_ROLLOUT_FUSED).waves_per_env == wpe, "asked for %d", wpe);
+        }
+    }
+    jx_render(x.c, nullptr, nullptr);
+    CHECK(fake::launches.back().waves_per_env == 1, "a render without frames n %d", n);
+  }
+  Ctx big(2048, 128);
+  CHECK(big.step().waves_per_env == 1 && big.rollout(JX_ROLLOUT_FUSED).waves_per_env == 1, "a full chip");
+  Ctx small(256, 64);  // 12 KB frames
+  CHECK(small.step().waves_per_env == 1, "small frames");
+}
+
+}  // namespace
+
+int main() {
+  check_waves_per_env();
+  std::printf("launch checks: %d failures\n", fake::fails);
+  return fake::fails != 0;
+}
