@@ -283,7 +283,10 @@ jx_status jx_get_state(const jx_ctx* ctx, void* host_buf, size_t bytes);
 jx_status jx_set_state(jx_ctx* ctx, const void* host_buf, size_t bytes);
 
 /* Launch mapping of later steps (this library's batching forms; results do
- * not depend on it).  JX_EINVAL for a mapping outside the limits above. */
+ * not depend on it).  JX_EINVAL for a mapping outside the limits above.
+ * jx_get_launch returns the mapping that per-step launches run, also where the
+ * library chose it: setting what it returned changes no step.  A fused rollout
+ * of a context whose mapping nobody set picks its own workgroups. */
 jx_status jx_set_launch(jx_ctx* ctx, const jx_launch* launch);
 jx_status jx_get_launch(const jx_ctx* ctx, jx_launch* launch);
 

@@ -476,11 +476,12 @@ jx_status jx_set_launch(jx_ctx* c, const jx_launch* l) {
 
 jx_status jx_get_launch(const jx_ctx* c, jx_launch* l) {
   if (!c || !l) return set_error(JX_EINVAL, "null argument");
-  l->form = c->launch.form;
-  l->waves_per_group = c->launch.waves_per_group;
-  l->groups_per_cu = c->launch.groups_per_cu;
-  l->store_mode = c->launch.store_mode;
-  l->waves_per_env = c->launch.waves_per_env;
+  const LaunchCfg m = step_launch(c);
+  l->form = m.form;
+  l->waves_per_group = m.waves_per_group;
+  l->groups_per_cu = m.groups_per_cu;
+  l->store_mode = m.store_mode;
+  l->waves_per_env = m.waves_per_env;
   return JX_OK;
 }
 

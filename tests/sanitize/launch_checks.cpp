@@ -82,10 +82,44 @@ void check_waves_per_env() {
   CHECK(small.step().waves_per_env == 1, "small frames");
 }
 
+// What jx_get_launch returns is what a step runs, and setting it changes no step.
+void check_reported_mapping() {
+  for (int n : {16, 700, 4096})
+    for (int px : {16, 128}) {
+      if (n == 4096 && px == 128) continue;
+      Ctx x(n, px);
+      const fake::Launch before = x.step();
+      jx_launch l{};
+      CHECK(jx_get_launch(x.c, &l) == JX_OK, "get_launch");
+      CHECK(l.form == before.cfg.form && l.waves_per_group == before.cfg.waves_per_group &&
+                l.store_mode == before.cfg.store_mode && l.waves_per_env == before.cfg.waves_per_env,
+            "n %d: reports groups of %d, runs %d", n, l.waves_per_group, before.cfg.waves_per_group);
+      x.set(1, 2, 4, 1, 1);
+      CHECK(jx_set_launch(x.c, &l) == JX_OK, "restored");
+      const fake::Launch after = x.step();
+      CHECK(after.cfg.form == before.cfg.form && after.cfg.waves_per_group == before.cfg.waves_per_group &&
+                after.cfg.store_mode == before.cfg.store_mode && after.waves_per_env == before.waves_per_env,
+            "n %d: a restored mapping runs groups of %d, before %d", n, after.cfg.waves_per_group,
+            before.cfg.waves_per_group);
+      jx_launch again{};
+      jx_get_launch(x.c, &again);
+      CHECK(std::memcmp(&again, &l, sizeof l) == 0, "n %d: reported again", n);
+    }
+  Ctx x(64, 16);
+  for (int form : {0, 1, 2}) {
+    x.set(form, 2, 3, 1, form == 0 ? 2 : 1);
+    jx_launch l{};
+    jx_get_launch(x.c, &l);
+    CHECK(l.form == form && l.waves_per_group == 2 && l.groups_per_cu == 3 && l.store_mode == 1 &&
+              l.waves_per_env == (form == 0 ? 2 : 1), "a mapping that was set, form %d", form);
+  }
+}
+
 }  // namespace
 
 int main() {
   check_waves_per_env();
+  check_reported_mapping();
   std::printf("launch checks: %d failures\n", fake::fails);
   return fake::fails != 0;
 }
