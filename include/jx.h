@@ -294,7 +294,10 @@ jx_status jx_get_launch(const jx_ctx* ctx, jx_launch* launch);
  * Sec. 3.1): times every candidate mapping over `iters` steps driven by
  * actions_dev[iters][n], writing frames into obs_scratch_dev (jx_obs_bytes()
  * bytes), checks that each candidate's frames, rewards, dones and state are
- * bit-identical to the default mapping's, and selects the fastest.  The env
+ * bit-identical to the default mapping's, and selects the fastest for per-step
+ * launches.  A fused rollout (JX_ROLLOUT_FUSED, or JX_ROLLOUT_GRAPH where it
+ * takes one launch) is not what was timed and keeps the library's own mapping,
+ * unless the pick is given to jx_set_launch.  The env
  * state is restored afterwards.  cache_path (nullable) is a text file of
  * previous choices keyed by device and workload shape.  *chosen (nullable)
  * receives the pick.  Synchronous. */

@@ -39,6 +39,7 @@ struct jx_ctx {
   int n_cu = 1;
   LaunchCfg launch{0, 1, 4, 0};
   bool launch_chosen = false;  // by jx_set_launch or jx_autotune
+  bool launch_tuned = false;   // by jx_autotune, which times per-step launches only
   uint32_t seq = 0;  // persistent launches enqueued on this context's stream
   // static scratch of jx_rollout_noalloc on this device (looked up at create)
   uint32_t* scratch = nullptr;
@@ -264,10 +265,12 @@ static jx_status rollout_fused(jx_ctx* c, const DevState& S, int32_t T, const ui
                                uint32_t seq) {
   LaunchCfg lc = c->launch;
   if (lc.form == JX_FORM_PIPELINE) lc = LaunchCfg{0, 4, 1, lc.store_mode};
-  // nobody's choice: 8 waves per workgroup fill the chip evenly where a stride
-  // runs (4096 envs of 64 x 64: 326 us for 32 steps, 342 with 4), 4 leave more
-  // room below that (2304: 267 and 212)
-  if (!c->launch_chosen) lc.waves_per_group = c->n > 12 * c->n_cu ? 8 : 4;
+  // Nobody's choice for this launch: 8 waves per workgroup fill the chip evenly where
+  // a stride runs (6144 envs of 84 x 84: 629 us for 24 steps, 670 with 4; 4096 of 64 x
+  // 64: 249 and 246), 4 leave more room below that (2304 of 64 x 64: 203 and 159).
+  // The tuner's pick among per-step launches is slower here: 16 steps of 2048 mixed
+  // shapes took 168 us under it and take 157, of 4096 64 x 64 frames 171 and 167.
+  if (!c->launch_chosen || c->launch_tuned) lc = LaunchCfg{0, c->n > 12 * c->n_cu ? 8 : 4, 1, 0};
   int rc = launch_rollout_fused(S, actions, obs, obs_stride, reward, done, prev_action, T, lc, c->max_side,
                                 c->n_cu, c->obs_off.back(), seq, c->stream);
   if (rc) return set_error(JX_EDEVICE, std::string("fused rollout launch: ") + kernel_error_string(rc));
@@ -470,6 +473,7 @@ jx_status jx_set_launch(jx_ctx* c, const jx_launch* l) {
   if (wpe > 1 && l->form != JX_FORM_PLAIN) return set_error(JX_EINVAL, "waves_per_env > 1 needs the plain form");
   if (wpe > w) return set_error(JX_EINVAL, "waves_per_env must not exceed waves_per_group");
   c->launch_chosen = true;
+  c->launch_tuned = false;
   c->launch = mapping(l->form, w, std::max(1, l->groups_per_cu), l->store_mode, wpe);
   return JX_OK;
 }
@@ -558,7 +562,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   LaunchCfg hit{};
   if (cache_lookup(cache_path, key, &hit)) {
     c->launch = mapping(hit.form, hit.waves_per_group, hit.groups_per_cu, hit.store_mode, hit.waves_per_env);
-    c->launch_chosen = true;
+    c->launch_chosen = c->launch_tuned = true;
     if (chosen) jx_get_launch(c, chosen);
     return JX_OK;
   }
@@ -666,6 +670,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
     return result;
   }
   c->launch = best;
+  c->launch_tuned = true;
   if (cache_path) {
     std::ofstream f(cache_path, std::ios::app);
     f << key << " " << best.form << " " << best.waves_per_group << " " << best.groups_per_cu << " "

@@ -2,6 +2,8 @@
 // library's host code over fake_hip.h, whose launches are recorded.
 #include "fake_hip.h"
 
+#include <unistd.h>
+
 #include "../../paper_2605_19926_amd/csrc/jx_abi.cpp"
 
 namespace {
@@ -115,11 +117,47 @@ void check_reported_mapping() {
   }
 }
 
+// The tuner's pick drives per-step launches; fused rollouts, which it does not
+// time, keep the library's own mapping until a caller sets the pick.
+int g_timed = 0, g_want = 0;
+double scripted_ms() { return g_timed++ / 2 == g_want ? 0.5 : 1.0; }  // each candidate is timed twice
+
+bool same_cfg(const LaunchCfg& a, const LaunchCfg& b) { return std::memcmp(&a, &b, sizeof a) == 0; }
+
+void check_tuned_mapping() {
+  const std::string cache = "/tmp/jx_launch_checks_" + std::to_string(getpid()) + ".txt";
+  fake::elapsed_ms = scripted_ms;
+  for (int want = 0; want < 48; ++want) {
+    std::remove(cache.c_str());
+    Ctx x(4096, 16);
+    const LaunchCfg fused = x.rollout(JX_ROLLOUT_FUSED).cfg, graph = x.rollout(JX_ROLLOUT_GRAPH).cfg;
+    g_timed = 0;
+    g_want = want;
+    jx_launch pick{}, again{};
+    CHECK(jx_autotune(x.c, x.act.data(), 8, x.frames(), cache.c_str(), &pick) == JX_OK, "tune: %s", jx_last_error());
+    for (int cached = 0; cached < 2; ++cached) {
+      const LaunchCfg step = x.step().cfg;
+      CHECK(step.form == pick.form && step.waves_per_group == pick.waves_per_group && step.store_mode == pick.store_mode &&
+                step.waves_per_env == pick.waves_per_env, "candidate %d: the step's mapping", want);
+      CHECK(same_cfg(x.rollout(JX_ROLLOUT_FUSED).cfg, fused), "candidate %d: fused rollout", want);
+      CHECK(same_cfg(x.rollout(JX_ROLLOUT_GRAPH).cfg, graph), "candidate %d: graph rollout", want);
+      if (cached == 0) CHECK(jx_autotune(x.c, x.act.data(), 8, x.frames(), cache.c_str(), &again) == JX_OK, "cached");
+    }
+    CHECK(std::memcmp(&pick, &again, sizeof pick) == 0, "candidate %d: the cached pick", want);
+    jx_set_launch(x.c, &pick);
+    const LaunchCfg set = x.rollout(JX_ROLLOUT_FUSED).cfg;
+    CHECK(pick.form == 2 || (set.form == pick.form && set.waves_per_group == pick.waves_per_group &&
+                             set.store_mode == pick.store_mode), "candidate %d: a pick that was set", want);
+  }
+  std::remove(cache.c_str());
+}
+
 }  // namespace
 
 int main() {
   check_waves_per_env();
   check_reported_mapping();
+  check_tuned_mapping();
   std::printf("launch checks: %d failures\n", fake::fails);
   return fake::fails != 0;
 }
