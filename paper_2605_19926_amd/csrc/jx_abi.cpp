@@ -600,6 +600,18 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   for (int p : {1, 2, 4})
     for (int g : {1, 2, 4})
       for (int s : {0, 1}) cands.push_back(mapping(2, p, g, s));
+  // candidates under the waves per env that they run, each once: where the library
+  // shares envs by itself, groups of 4 and 8 with 1 asked for are those with 4
+  std::vector<LaunchCfg> all;
+  all.swap(cands);
+  for (LaunchCfg& l : all) {
+    if (l.form == JX_FORM_PLAIN) l.waves_per_env = step_waves_per_env(l, true, n, ob, c->max_w, c->n_cu);
+    auto runs_as = [&](const LaunchCfg& o) {
+      return o.form == l.form && o.waves_per_group == l.waves_per_group && o.groups_per_cu == l.groups_per_cu &&
+             o.store_mode == l.store_mode && o.waves_per_env == l.waves_per_env;
+    };
+    if (std::none_of(cands.begin(), cands.end(), runs_as)) cands.push_back(l);
+  }
   const LaunchCfg keep = c->launch;
   const bool keep_chosen = c->launch_chosen;
   c->launch_chosen = true;

@@ -152,12 +152,43 @@ void check_tuned_mapping() {
   std::remove(cache.c_str());
 }
 
+// Every candidate is named by the waves per env that it runs, and timed once.
+void check_tuner_candidates() {
+  fake::elapsed_ms = scripted_ms;
+  for (int n : {128, 1024, 2048})  // 4 waves where 1 is asked for, up to 4 envs per CU
+    for (int want = 0; want < 44; ++want) {
+      if (n != 128 && want % 9) continue;
+      Ctx x(n, n == 2048 ? 16 : 128, 1);
+      const size_t first = fake::launches.size();
+      g_timed = 0;
+      g_want = want;
+      jx_launch pick{};
+      CHECK(jx_autotune(x.c, x.act.data(), 1, x.frames(), nullptr, &pick) == JX_OK, "tune: %s", jx_last_error());
+      std::vector<std::string> seen;
+      for (size_t k = first; k < fake::launches.size(); k += 2) {
+        const fake::Launch& l = fake::launches[k];
+        CHECK(l.cfg.form != 0 || l.cfg.waves_per_env == l.waves_per_env, "n %d: groups of %d are named %d, run %d", n,
+              l.cfg.waves_per_group, l.cfg.waves_per_env, l.waves_per_env);
+        char key[64];
+        std::snprintf(key, sizeof key, "%d/%d/%d/%d/%d", l.cfg.form, l.cfg.waves_per_group, l.cfg.groups_per_cu,
+                      l.cfg.store_mode, l.waves_per_env);
+        CHECK(std::find(seen.begin(), seen.end(), key) == seen.end(), "n %d: %s is timed twice", n, key);
+        seen.push_back(key);
+      }
+      CHECK(seen.size() == (n == 2048 ? 48u : 46u), "n %d: %zu candidates", n, seen.size());
+      const fake::Launch s = x.step();
+      CHECK(pick.form != 0 || s.waves_per_env == pick.waves_per_env, "n %d: picked %d waves per env, runs %d", n,
+            pick.waves_per_env, s.waves_per_env);
+    }
+}
+
 }  // namespace
 
 int main() {
   check_waves_per_env();
   check_reported_mapping();
   check_tuned_mapping();
+  check_tuner_candidates();
   std::printf("launch checks: %d failures\n", fake::fails);
   return fake::fails != 0;
 }
