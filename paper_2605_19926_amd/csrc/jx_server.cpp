@@ -369,6 +369,7 @@ void admitter_main(jx_server* s) {
     s->stats.clients_pending -= 1;
     if (st != JX_OK) {
       s->fatal = "admission failed: " + std::string(jx_last_error());
+      if (c->closing) s->closing -= 1;  // (reap_closed releases admitted clients)
       c->st = CLOSED;
       for (auto& r : c->queue) {
         r->status = 3;
@@ -854,6 +855,7 @@ jx_status open_client(jx_server* s, int32_t n_envs, const uint64_t* seeds, const
   jx_status st = activate(s, cp);
   lk.lock();
   if (st != JX_OK) {
+    if (cp->closing) s->closing -= 1;
     free_client_memory(s, cp);
     for (auto& r : cp->queue) {
       r->status = 3;
@@ -998,8 +1000,8 @@ jx_status jx_server_close(jx_server* s, int32_t client) {
     s->clients.erase(it);
   } else {
     // admitted (or still to be admitted, with queued requests): released once
-    // its queued requests have run
-    if (!c->closing) s->closing += 1;
+    // its queued requests have run; one whose admission failed holds nothing
+    if (!c->closing && c->st != CLOSED) s->closing += 1;
     c->closing = true;
   }
   wake_sched(s);
