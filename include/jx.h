@@ -131,8 +131,9 @@ typedef struct {
                               batches and large frames use more of the chip;
                               results do not change.  With 1 the library takes 2
                               or 4 by itself, never more than waves_per_group,
-                              where a batch leaves most of the chip idle: 1 wave
-                              per group is 1 wave per env. */
+                              where a batch leaves most of the chip idle (a
+                              render does so whatever is set here): 1 wave per
+                              group is 1 wave per env. */
 } jx_launch;
 
 /* Per-column record of the last render (tests and tools).  hit = tile id of the

@@ -605,7 +605,7 @@ extern "C" jx_status jx_autotune(jx_ctx* c, const uint8_t* actions, int32_t iter
   std::vector<LaunchCfg> all;
   all.swap(cands);
   for (LaunchCfg& l : all) {
-    if (l.form == JX_FORM_PLAIN) l.waves_per_env = step_waves_per_env(l, true, n, ob, c->max_w, c->n_cu);
+    if (l.form == JX_FORM_PLAIN) l.waves_per_env = step_waves_per_env(l, MODE_STEP, true, n, ob, c->max_w, c->n_cu);
     auto runs_as = [&](const LaunchCfg& o) {
       return o.form == l.form && o.waves_per_group == l.waves_per_group && o.groups_per_cu == l.groups_per_cu &&
              o.store_mode == l.store_mode && o.waves_per_env == l.waves_per_env;

@@ -134,15 +134,21 @@ struct LaunchCfg {
 };
 
 // Waves per env of a per-step launch (`frames`: a step or render that writes them).
+// The waves that were asked for are a step's.  A render has less for one wave to do
+// before the others can write: under 4 waves asked for, 9143 renders of 32 x 32 took
+// 33.6 us against 15.8 with one, 4096 of 64 x 64 21.8 against 13.4, 2048 of 84 x 84
+// 16.0 against 13.8; 512 of 128 x 128 10.0 against 12.6.  So it takes them where a
+// mapping left to the library does.
 // Where one wave is asked for, more are allowed and the batch leaves most of the
 // chip idle, frames of 16 KB and more take four: one wave would write each longer
 // than the rest of the step lasts.  us per step with 1 and 4 waves: 256 envs of
 // 64 x 64 float32 12.7, 10.8, 768 of them 18.0, 17.9, 1024 20.4, 20.6; with two
 // casting waves 1024 of 128 x 128 bytes 16.2, 15.2; 128 of 128 x 128 float32 26.4,
 // 15.8; 768 of 84 x 84 bytes 21.3, 21.0.
-inline int step_waves_per_env(const LaunchCfg& lc, bool frames, int n, int64_t frames_bytes, int max_w, int n_cu) {
+inline int step_waves_per_env(const LaunchCfg& lc, int mode, bool frames, int n, int64_t frames_bytes, int max_w,
+                              int n_cu) {
   if (!frames) return 1;
-  if (lc.waves_per_env > 1) return lc.waves_per_env;
+  if (lc.waves_per_env > 1 && mode == MODE_STEP) return lc.waves_per_env;
   const bool idle = frames_bytes >= (int64_t)n * 16384 && n <= (max_w > 64 ? 4 : 3) * n_cu;
   return idle && lc.most_waves_per_env >= 4 ? 4 : 1;
 }

@@ -196,7 +196,8 @@ int launch_batch(const DevState& s, const DevIo& io,
   // steps and renders that write frames (resets and debug records take one).
   if (lc.form == 0 || s.obs_fmt != 0) {
     const bool frames = io.mode != MODE_RESET && io.obs != nullptr && io.dbg == nullptr;
-    const int wpe = step_waves_per_env(lc, frames, s.n, frames_bytes, max_w, n_cu), wpg = wpb < wpe ? wpe : wpb;
+    const int wpe = step_waves_per_env(lc, io.mode, frames, s.n, frames_bytes, max_w, n_cu);
+    const int wpg = wpb < wpe ? wpe : wpb;
     return by_shape<PlainL>(s, max_side, io, wpg, wpe, st);
   }
   if (lc.form == 2) {

@@ -92,7 +92,7 @@ namespace jx {
 int launch_batch(const DevState& s, const DevIo& io, const LaunchCfg& lc, int, int max_w, int64_t frames_bytes, int n_cu,
                  uint32_t, void*) {
   const bool frames = io.mode != MODE_RESET && io.obs != nullptr && io.dbg == nullptr;
-  FAKE_RECORD({"batch", lc, io.mode, s.n, 1, step_waves_per_env(lc, frames, s.n, frames_bytes, max_w, n_cu)});
+  FAKE_RECORD({"batch", lc, io.mode, s.n, 1, step_waves_per_env(lc, io.mode, frames, s.n, frames_bytes, max_w, n_cu)});
   (void)frames, (void)max_w, (void)frames_bytes, (void)n_cu, (void)lc, (void)s;
   return 0;
 }

@@ -49,6 +49,10 @@ struct Ctx {
     CHECK(jx_step(c, act.data(), frames(), rew.data(), done.data(), nullptr) == JX_OK, "step: %s", jx_last_error());
     return fake::launches.back();
   }
+  fake::Launch render() {
+    CHECK(jx_render(c, frames(), nullptr) == JX_OK, "render: %s", jx_last_error());
+    return fake::launches.back();
+  }
   fake::Launch rollout(int flags, int T = 8) {
     CHECK(jx_rollout(c, T, act.data(), frames(), 0, rew.data(), done.data(), nullptr, flags) == JX_OK, "rollout: %s",
           jx_last_error());
@@ -82,6 +86,24 @@ void check_waves_per_env() {
   CHECK(big.step().waves_per_env == 1 && big.rollout(JX_ROLLOUT_FUSED).waves_per_env == 1, "a full chip");
   Ctx small(256, 64);  // 12 KB frames
   CHECK(small.step().waves_per_env == 1, "small frames");
+}
+
+// A render shares envs where the batch leaves the chip idle, whatever is asked of steps.
+void check_renders() {
+  for (int n : {100, 768, 1024, 1025, 4096})
+    for (int px : {16, 64, 84, 128}) {
+      if (n == 4096 && px == 128) continue;
+      Ctx x(n, px, 1);
+      const int idle = px > 64 ? (n <= 1024 ? 4 : 1) : 1;
+      CHECK(x.render().waves_per_env == idle, "left to the library: n %d, %d px", n, px);
+      for (int wpg : {2, 4, 8})
+        for (int wpe : {1, 2, 4}) {
+          if (wpe > wpg) continue;
+          x.set(0, wpg, 1, 0, wpe);
+          CHECK(x.render().waves_per_env == (wpg >= 4 ? idle : 1), "groups of %d, %d asked for: n %d, %d px", wpg, wpe, n, px);
+          if (wpe > 1) CHECK(x.step().waves_per_env == wpe, "a step takes the %d asked for", wpe);
+        }
+    }
 }
 
 // What jx_get_launch returns is what a step runs, and setting it changes no step.
@@ -186,6 +208,7 @@ void check_tuner_candidates() {
 
 int main() {
   check_waves_per_env();
+  check_renders();
   check_reported_mapping();
   check_tuned_mapping();
   check_tuner_candidates();
