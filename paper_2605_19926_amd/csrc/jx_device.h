@@ -789,7 +789,23 @@ __device__ __forceinline__ ColGroupF<FMT> col_group_f(const uint32_t* lcol, cons
   return g;
 }
 
-// Stores one row's dwords of a lane: p is the lane's place in plane 0.
+// One vector per lane, past the caches on request.  The branches hold something that
+// tells them apart, else the compiler makes one store of them and drops the request.
+template <typename V>
+__device__ __forceinline__ void store_vector(GlobalU32* q, V v, int nt) {
+  typedef __attribute__((address_space(1))) V G;
+  if (nt) {
+    asm volatile("; past the caches");
+    __builtin_nontemporal_store(v, (G*)q);
+    asm volatile("; past the caches");
+  } else {
+    *(G*)q = v;
+  }
+}
+
+// Stores one row's dwords of a lane: p is the lane's place in plane 0.  Planes take
+// one vector per lane: left to the compiler, which cannot know the alignment, the
+// fused kernels' non-temporal stores were single dwords and triples.
 template <int FMT>
 __device__ __forceinline__ void store_words(uint8_t* p, int64_t plane, const uint32_t (&v)[ObsFmt<FMT>::kWords],
                                             int nt) {
@@ -798,20 +814,17 @@ __device__ __forceinline__ void store_words(uint8_t* p, int64_t plane, const uin
 #pragma unroll
   for (int r = 0; r < runs; ++r) {
     GlobalU32* q = (GlobalU32*)(p + r * plane);
-    if (nt) {
+    const uint32_t* w = v + r * per;
+    if constexpr (per == 4) {
+      store_vector(q, u32x4{w[0], w[1], w[2], w[3]}, nt);
+    } else if constexpr (per == 2) {
+      store_vector(q, u32x2{w[0], w[1]}, nt);
+    } else if (nt) {
 #pragma unroll
-      for (int k = 0; k < per; ++k) __builtin_nontemporal_store(v[r * per + k], q + k);
-    } else if (per % 4 == 0) {
-#pragma unroll
-      for (int k = 0; k < per; k += 4)
-        *(GlobalU32x4*)(q + k) = u32x4{v[r * per + k], v[r * per + k + 1], v[r * per + k + 2], v[r * per + k + 3]};
-    } else if (per % 2 == 0) {
-#pragma unroll
-      for (int k = 0; k < per; k += 2)
-        *(GlobalU32x2*)(q + k) = u32x2{v[r * per + k], v[r * per + k + 1]};
+      for (int k = 0; k < per; ++k) __builtin_nontemporal_store(w[k], q + k);
     } else {
 #pragma unroll
-      for (int k = 0; k < per; ++k) q[k] = v[r * per + k];
+      for (int k = 0; k < per; ++k) q[k] = w[k];
     }
   }
 }
