@@ -301,12 +301,12 @@ jx_status jx_rollout(jx_ctx* c, int32_t T, const uint8_t* actions, uint8_t* obs,
   // One launch for all steps.  JX_ROLLOUT_GRAPH asks for one launch in the caller's
   // time and takes it too: it carries each env through its steps on chip, where a
   // graph of per-step launches pays about 2 us between them and the load of every
-  // env's state each time (64 steps of 1024 envs of 64 x 64: 610 us as a graph, 205
+  // env's state each time (64 steps of 1024 envs of 64 x 64: 610 us as a graph, 196
   // fused; 32 steps of 16384: 1327 and 1301).  A single step, and up to 3 of very
   // many envs with larger byte frames, go launch by launch, where more waves fit on
   // the chip and the host stays ahead (16384 envs of 64 x 64: 1 step 37 us, 54
-  // fused; 2 steps 85 and 104; 4 steps 166 and 172).
-  const bool few = T == 1 || (T < 4 && c->n > 32 * c->n_cu && c->S.obs_fmt == 0 &&
+  // fused; 2 steps 85 and 104, NCHW 81 and 110; 4 steps 166 and 172).
+  const bool few = T == 1 || (T < 4 && c->n > 32 * c->n_cu && obs_elem_bytes(c->S.obs_fmt) == 1 &&
                               c->obs_off.back() >= (int64_t)c->n * 8192);
   if ((flags & JX_ROLLOUT_FUSED) || ((flags & JX_ROLLOUT_GRAPH) && !few)) {
     st = rollout_fused(c, c->S, T, actions, obs, obs_stride, reward, done, prev_action, c->seq);

@@ -15,8 +15,10 @@ struct Ctx {
   std::vector<float> rew;
   int n;
   jx_env_cfg cfg{};
-  Ctx(int n_envs, int px, int T = 8) : n(n_envs) {
+  Ctx(int n_envs, int px, int T = 8, int layout = 0, int dtype = 0) : n(n_envs) {
     cfg.side = 8;
+    cfg.obs_layout = layout;
+    cfg.obs_dtype = dtype;
     cfg.n_colors = 8;
     cfg.goal_sprite = 1;
     cfg.obs_h = cfg.obs_w = px;
@@ -139,6 +141,26 @@ void check_reported_mapping() {
   }
 }
 
+// The graph flag takes one launch, but for a single step and a few steps of very many
+// envs with larger byte frames.
+void check_graph_flag() {
+  for (int layout : {0, 1})
+    for (int dtype : {0, 1, 2})
+      for (int px : {16, 64})
+        for (int n : {8192, 8193}) {
+          if (px * px * (dtype + 1) > 64 * 64 && n == 8192) continue;
+          Ctx x(n, px, 4, layout, dtype);
+          for (int T : {1, 2, 3, 4}) {
+            const size_t first = fake::launches.size();
+            x.rollout(JX_ROLLOUT_GRAPH, T);
+            const bool steps = T == 1 || (T < 4 && n > 8192 && dtype == 0 && px == 64);
+            const size_t made = fake::launches.size() - first;
+            CHECK(made == (steps ? (size_t)T : 1u) && fake::launches.back().kind == (steps ? "batch" : "fused"),
+                  "layout %d, type %d, %d px, n %d, T %d: %zu launches", layout, dtype, px, n, T, made);
+          }
+        }
+}
+
 // The tuner's pick drives per-step launches; fused rollouts, which it does not
 // time, keep the library's own mapping until a caller sets the pick.
 int g_timed = 0, g_want = 0;
@@ -210,6 +232,7 @@ int main() {
   check_waves_per_env();
   check_renders();
   check_reported_mapping();
+  check_graph_flag();
   check_tuned_mapping();
   check_tuner_candidates();
   std::printf("launch checks: %d failures\n", fake::fails);
