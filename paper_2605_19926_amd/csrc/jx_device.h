@@ -1082,7 +1082,7 @@ constexpr int kWaitTwoPairs = 0x0F74;
 // (Q = W / 4 groups, di = 64 / Q), so each lane's group is fixed.
 template <int FMT>
 __device__ void fill_frame_f(const uint32_t* lcol, const uint32_t* lcvt, uint8_t* base, int W, int H, int lane,
-                             int nt, int part, int parts) {
+                             int nt, int part, int parts, int n) {
   using F = ObsFmt<FMT>;
   const int H2 = H >> 1;
   const int64_t rowb = F::row_bytes(W), plane = (int64_t)H * W * F::kElem;
@@ -1091,11 +1091,12 @@ __device__ void fill_frame_f(const uint32_t* lcol, const uint32_t* lcvt, uint8_t
   // one pass and the rest, several rows at a time, in a second one.  The second
   // pass is fewer instructions while the rest is short, but its lines are gone
   // from the L2 when it comes unless few waves write: with one wave per frame
-  // 1500 fused envs of 84x84 take 212 us against 347 (8 steps), and where waves share a
-  // frame (512 envs or fewer) 200 of 68x68 take 41 against 32, of 84x84 47.4 against
-  // 39.5, of 100x100 53.7 against 57.3, 500 of 100x100 108 against 152.
-  constexpr int kTwoPassW = 84;
-  if (F::kCols == 1 && W > 64 && (parts == 1 || W > kTwoPassW)) {
+  // 1500 fused envs of 84x84 take 212 us against 347 (8 steps).  Where waves share a
+  // frame 200 of 68x68 take 41 against 32, of 84x84 47.4 against 39.5, of 100x100 53.7
+  // against 57.3; 700 of 68x68 63 against 58, of 76x76 89 against 110, of 84x84 111
+  // against 147; 1000 of 68x68 103 against 126, of 84x84 161 against 219.
+  const int two_pass_n = W <= 72 ? 768 : 512;
+  if (F::kCols == 1 && W > 64 && (parts == 1 || W > 84 || n > two_pass_n)) {
     const int l2 = lane + 64;
     const bool two = l2 < W;
     const ColGroupF<FMT> g = col_group_f<FMT>(lcol, lcvt, lane), g2 = col_group_f<FMT>(lcol, lcvt, two ? l2 : lane);
@@ -1134,11 +1135,12 @@ __device__ void fill_frame_f(const uint32_t* lcol, const uint32_t* lcvt, uint8_t
 }
 
 // BOUND: keep at most two row pairs of the wave's stores in flight (see kWaitTwoPairs).
+// n: envs of the batch.
 template <int FMT, bool BOUND>
 __device__ void fill_frame(const uint32_t* lcol, const uint32_t* lcvt, uint8_t* base, int W, int H, int lane,
-                           int nt, int part = 0, int parts = 1) {
+                           int nt, int part = 0, int parts = 1, int n = 1) {
   if constexpr (FMT != 0) {
-    fill_frame_f<FMT>(lcol, lcvt, base, W, H, lane, nt, part, parts);
+    fill_frame_f<FMT>(lcol, lcvt, base, W, H, lane, nt, part, parts, n);
     return;
   }
   // lane -> (column group cq, first distance i); the wave's di * Q lanes
@@ -1527,7 +1529,7 @@ __device__ __forceinline__ void process_env(const DevState& S, const DevIo& io, 
   if (parts > 1) __syncthreads();
   if (!live) return;
   o.obs_off = obs_off_of(S, env);
-  if (io.obs) fill_frame<FMT, false>(lcol, lcvt, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode, part, parts);
+  if (io.obs) fill_frame<FMT, false>(lcol, lcvt, io.obs + o.obs_off, o.W, o.H, lane, io.store_mode, part, parts, S.n);
   if (part == 0) write_back(S, io, o, lane);
 }
 

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(64 * WPE) void k_roll_split(DevState S, RollIo r) {
         __syncthreads();  // step t's records are in buffer t & 1
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        fill_frame<FMT, false>(scol[t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, WPE - casters);
+        fill_frame<FMT, false>(scol[t & 1], scvt, at, W, H, ln, r.store_mode, part - casters, WPE - casters, n);
         at += r.obs_stride;
       }
       __syncthreads();
