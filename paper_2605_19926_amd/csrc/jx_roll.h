@@ -18,7 +18,8 @@ struct RollIo {
 
 // Kernels of jx_roll_narrow.hip, by map side and ASCII support: 2 or 4 waves per
 // env (wpe), and 4 waves per SIMD of one-wave envs (byte frames of mazes).
-int launch_roll_split(const DevState& s, int max_side, const RollIo& r, int groups, int wpe, hipStream_t st);
+int launch_roll_split(const DevState& s, int max_side, const RollIo& r, int groups, int wpe, int64_t frames_bytes, int n_cu,
+                      hipStream_t st);
 int launch_roll_dense(const DevState& s, int max_side, const RollIo& r, int wpb, int groups, hipStream_t st);
 
 namespace {

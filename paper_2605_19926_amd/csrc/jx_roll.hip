@@ -103,7 +103,7 @@ int launch_rollout_fused(const DevState& s, const uint8_t* act, uint8_t* obs, in
   }
   const int most = n_cu * (per_cu > 0 ? per_cu : 1);
   if (groups > most) groups = most;
-  if (wpe > 1) return launch_roll_split(s, max_side, r, groups, wpe, st);
+  if (wpe > 1) return launch_roll_split(s, max_side, r, groups, wpe, frames_bytes, n_cu, st);
   if (dense) return launch_roll_dense(s, max_side, r, wpb, groups, st);
   return by_shape<RollL>(s, max_side, r, wpb, groups, lds, st);
 }

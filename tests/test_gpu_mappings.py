@@ -108,3 +108,15 @@ def test_full_chip_rollouts_in_every_format(layout, dtype, base):
     cfg = W.env_cfg(obs_h=34, obs_w=36, episode_cap=5, obs_layout=layout, obs_dtype=dtype, **base)
     for n in (1537, 2050):
         assert _same(_run(cfg, n, 4, None, True), _run(cfg, n, 4, ONE, False)), n
+
+
+@pytest.mark.parametrize("base", [dict(ROOMS), dict(TREE), dict(side=40, loop_frac=0.2, goal_sprite=1)])
+@pytest.mark.parametrize("layout,dtype", [f for f in FORMATS if f[1]])
+def test_large_frames_under_two_waves(layout, dtype, base):
+    """Frames around the size from which the casting wave writes a third, up to an env
+    per CU: odd numbers of row-pair blocks, idle lanes, a last block for one wave only."""
+    for n, h, w in ((5, 84, 84), (3, 128, 128), (2, 62, 112), (2, 126, 72), (256, 90, 76), (257, 90, 76)):
+        cfg = W.env_cfg(obs_h=h, obs_w=w, episode_cap=4, obs_layout=layout, obs_dtype=dtype, **base)
+        T = 9 if n < 200 else 3
+        want = _run(cfg, n, T, ONE, False)
+        assert _same(_run(cfg, n, T, dict(waves_per_group=4, waves_per_env=2), True), want), (n, h, w)
