@@ -494,8 +494,8 @@ __device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint
     const int spawn = n_s ? mask_select(spawnm, sm_draw(s, n_s), N) : mask_select(freem, sm_draw(s, n_free), N);
     const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
     ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
-    ep.x = (float)(n_free ? td.col(spawn) : -1) + 0.5f;
-    ep.y = (float)(n_free ? td.row(spawn) : -1) + 0.5f;
+    ep.x = (float)td.col(spawn) + 0.5f;
+    ep.y = (float)td.row(spawn) + 0.5f;
     const uint32_t n_g = mask_count(goalm);
     if (n_g) {
       ep.goal = mask_select(goalm, sm_draw(s, n_g), N);
@@ -512,8 +512,8 @@ __device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint
   const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
   ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
   // (a map without floor, which only a loaded state can hold: off the map, goalless)
-  ep.x = (float)(n_free ? td.col(spawn) : -1) + 0.5f;
-  ep.y = (float)(n_free ? td.row(spawn) : -1) + 0.5f;
+  ep.x = (float)td.col(spawn) + 0.5f;
+  ep.y = (float)td.row(spawn) + 0.5f;
 
   // goal: the first of the farthest tiles; door: the first tile halfway on a
   // shortest path to it; key: in the region that the shut door leaves to the spawn
@@ -1423,8 +1423,9 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
     uint32_t* lbits = lcol + 128 * part;
     const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, (MAXN > 16), uint32_t>(cf, td, lmap, lbits, seed, e, lane)
                                             : episode_reset<ASC, (MAXN > 16), uint64_t>(cf, td, lmap, lbits, seed, e, lane);
-    x = n.x;
-    y = n.y;
+    // (no goal: a map without floor, which only a loaded state can hold; off the map)
+    x = n.goal < 0 ? -0.5f : n.x;
+    y = n.goal < 0 ? -0.5f : n.y;
     th = n.th;
     goal = n.goal;
     door = n.door;
