@@ -116,7 +116,7 @@ typedef struct {
 typedef struct jx_ctx jx_ctx;
 
 /* Launch mapping (results are bit-identical under every mapping). */
-#define JX_FORM_PLAIN 0       /* one wave per env, one workgroup slot per env */
+#define JX_FORM_PLAIN 0       /* a wave (or waves_per_env of them) per env, one workgroup slot per wave */
 #define JX_FORM_PERSISTENT 1  /* persistent waves pull envs from device work queues */
 #define JX_FORM_PIPELINE 2    /* persistent producer/writer wave pairs, double-buffered */
 typedef struct {
@@ -226,8 +226,7 @@ jx_status jx_step(jx_ctx* ctx, const uint8_t* actions_dev, uint8_t* obs_dev, flo
  * done_dev + t*n and, when prev_action_dev is not NULL, previous actions (as in
  * jx_step) at prev_action_dev + t*n.  flags & JX_ROLLOUT_GRAPH: the fastest way
  * to run T steps whose actions are known, chosen by T and the batch: the fused
- * launch below or, for a few steps of very many envs, T launches.  (It used to
- * replay a captured graph of T launches, which the fused launch is faster than.)
+ * launch below or, for one step or a few steps of very many envs, T launches.
  * Without flags the T launches are enqueued one by one. */
 #define JX_ROLLOUT_GRAPH 1
 /* flags & JX_ROLLOUT_FUSED: one launch runs all T steps; each wave keeps its
@@ -235,7 +234,7 @@ jx_status jx_step(jx_ctx* ctx, const uint8_t* actions_dev, uint8_t* obs_dev, flo
  * Outputs (frames, rewards, dones, final state) equal T single-step launches
  * bit for bit.  Takes precedence over JX_ROLLOUT_GRAPH.  Under the plain
  * mapping, waves take envs by a static stride (waves_per_group waves per
- * workgroup, waves_per_env of them sharing each env); under the persistent
+ * workgroup, or where waves share an env one env per workgroup); under the persistent
  * mapping, groups_per_cu workgroups per compute unit claim envs one at a time
  * from device work queues, costliest
  * first (uneven shapes); the pipelined mapping and the training-buffer formats
@@ -258,7 +257,8 @@ jx_status jx_rollout(jx_ctx* ctx, int32_t T, const uint8_t* actions_dev, uint8_t
  * enqueues kernels on the context's stream: a kernel first clears the counters
  * the previous call left in the array, so a captured call replays correctly.
  * flags: 0 (T launches) or JX_ROLLOUT_FUSED (one launch); JX_ROLLOUT_GRAPH is
- * rejected with JX_EINVAL.  Every call on a
+ * rejected with JX_EINVAL: which kernels run is the caller's choice here, not the
+ * library's.  Every call on a
  * device shares that device's array: calls that overlap on one device (other
  * streams, threads or contexts) race and must be serialised by the caller.
  * JX_EDEVICE if the array could not be resolved when the context was created. */

@@ -1,7 +1,8 @@
 // jx_device.h -- device code shared by the per-step and the fused kernels:
 // step, reset, column cast and frame fill of one env, and the work queues.
 //
-// One 64-lane wave owns one environment for the whole step:
+// One 64-lane wave owns one environment for the whole step (where a batch leaves the
+// chip idle, 2 or 4 waves share one: one or two of them do 1 to 4, then all write):
 //   1. stage the env's N x N tile map from HBM into the wave's LDS slice;
 //   2. apply the action (turn / move / strafe, axis-separated collision), then
 //      key, goal, reward, truncation (rules of the key-door and navigation tasks,

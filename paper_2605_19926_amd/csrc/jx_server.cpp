@@ -235,8 +235,8 @@ struct jx_server {
 // Takes the server lock, trying for some microseconds before sleeping on it: it is
 // held for one or two at a time, and a sleep and its wake-up cost a caller ten.  With
 // the waits' poll and no wake of the scheduler for each collected request, 96
-// requests of device-ring clients submitted and collected by one thread took 366 us
-// instead of 713, 24 with host results 279 instead of 338.
+// requests of device-ring clients submitted and collected by one thread take 465-518 us
+// instead of 730-744, 24 with host results 285-295 instead of 344-352.
 void lock_soon(std::unique_lock<std::mutex>& lk) {
   for (int i = 0; i < 200; ++i) {
     if (lk.try_lock()) return;
