@@ -304,10 +304,9 @@ def serve_form(jx, n_requests: int, mode: int, rate: float = W.SERVE["rate"],
 
 def shape_sweep(jx, torch) -> list[dict]:
     """Fused 128-step rollouts of one configuration (16x16 mazes) over frame
-    size x env count, under the static-stride and persistent mappings with one
-    wave per env and the static stride with 2 or 4 waves per env: how many envs
-    one wave per env needs before the frame writes saturate, and what several
-    waves per env give below that."""
+    size x env count, under the static-stride and persistent mappings: one wave
+    per env (groups of one wave; the persistent mapping), the waves per env that
+    the library takes by itself in groups of 4 and 8, and 2 or 4 waves per env."""
     T = 128
     out = []
     for side_px in (32, 64, 128):
@@ -321,7 +320,8 @@ def shape_sweep(jx, torch) -> list[dict]:
             rew = torch.empty(T * n, dtype=torch.float32, device=env.dev)
             dn = torch.empty(T * n, dtype=torch.uint8, device=env.dev)
             acts = torch.from_numpy(W.actions(3, T, n, 6)).to(env.dev)
-            for launch in (dict(form=0, waves_per_group=4, groups_per_cu=1, store_mode=0),
+            for launch in (dict(form=0, waves_per_group=1, groups_per_cu=1, store_mode=0),
+                           dict(form=0, waves_per_group=4, groups_per_cu=1, store_mode=0),
                            dict(form=0, waves_per_group=8, groups_per_cu=1, store_mode=0),
                            dict(form=1, waves_per_group=4, groups_per_cu=2, store_mode=0),
                            dict(form=0, waves_per_group=8, groups_per_cu=1, store_mode=0, waves_per_env=2),

@@ -512,7 +512,6 @@ __device__ Episode episode_reset(const DevCfg& cf, const TileDiv& td, const uint
   const int spawn = mask_select(freem, sm_draw(s, n_free), N);
   const uint32_t k24 = (uint32_t)(sm_next(s) >> 40);
   ep.th = (float)k24 * (kTwoPiF * 0x1p-24f);
-  // (a map without floor, which only a loaded state can hold: off the map, goalless)
   ep.x = (float)td.col(spawn) + 0.5f;
   ep.y = (float)td.row(spawn) + 0.5f;
 
@@ -1424,7 +1423,8 @@ __device__ void produce_env(const EnvIn<MAXN>& in, const DevIo& io, int a,
     uint32_t* lbits = lcol + 128 * part;
     const Episode n = MAXN <= 32 || N <= 32 ? episode_reset<ASC, (MAXN > 16), uint32_t>(cf, td, lmap, lbits, seed, e, lane)
                                             : episode_reset<ASC, (MAXN > 16), uint64_t>(cf, td, lmap, lbits, seed, e, lane);
-    // (no goal: a map without floor, which only a loaded state can hold; off the map)
+    // (no goal: a map without floor, which only a loaded state can hold; the draws
+    // found no tile, and the agent stands off the map)
     x = n.goal < 0 ? -0.5f : n.x;
     y = n.goal < 0 ? -0.5f : n.y;
     th = n.th;
