@@ -42,7 +42,11 @@ __global__ __launch_bounds__(64 * WPE) void k_roll_split(DevState S, RollIo r) {
       H = (int)uniform_u((uint32_t)cf.obs_h);
       obs_off = obs_off_of(Q, env);
     }
-    const int casters = WPE == 4 && W > 64 ? 2 : 1;
+    // two of four waves cast rows of more than 64 columns, unless float frames of many
+    // envs wait for their writers (1000, 1500 envs for 8 steps with two and with one
+    // casting: 100 x 100 float32 NCHW 240 and 229, 366 and 346 us, 84 x 84 NHWC 161 and
+    // 156, 250 and 237; 600 of 84 x 84 bfloat16 41 and 45, 1500 of bytes 51 and 60)
+    const int casters = WPE == 4 && W > 64 && (FMT % 3 == 0 || n <= 768) ? 2 : 1;
     uint8_t* at = r.obs + obs_off;
     if (part < casters) {
       uint8_t* lmap = smap[WPE == 4 ? part : 0] + guard_bytes(MAXN);

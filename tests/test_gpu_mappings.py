@@ -120,3 +120,12 @@ def test_large_frames_under_two_waves(layout, dtype, base):
         T = 9 if n < 200 else 3
         want = _run(cfg, n, T, ONE, False)
         assert _same(_run(cfg, n, T, dict(waves_per_group=4, waves_per_env=2), True), want), (n, h, w)
+
+
+@pytest.mark.parametrize("layout,dtype", FORMATS)
+@pytest.mark.parametrize("n", [768, 769])
+def test_wide_rows_under_four_waves(layout, dtype, n):
+    """Around the batch from which one wave of four casts the wide rows of float frames."""
+    cfg = W.env_cfg(obs_h=10, obs_w=72, episode_cap=4, obs_layout=layout, obs_dtype=dtype, **TREE)
+    want = _run(cfg, n, 6, ONE, False)
+    assert _same(_run(cfg, n, 6, dict(waves_per_group=4, waves_per_env=4), True), want)
